@@ -773,22 +773,46 @@ __device__ __forceinline__ void trace_item(const TraceView& v, int64_t k, int* s
 #define kFiveWaves kTraceWaves(false)
 #define kBatchWaves(lambert, phased) __attribute__((amdgpu_waves_per_eu((phased) ? 8 : ((lambert) ? 6 : 5))))
 
-// Workgroups are dispatched to the 8 XCDs round-robin.  Work items are
-// permuted so that XCD q receives the q-th contiguous eighth of the items:
-// rays of one screen region then share their XCD's L2 for the BVH levels
-// near the leaves, instead of every L2 holding the whole screen's working
-// set.  Workgroup ids past the last multiple of 8 keep their place.
+// Workgroups are dispatched to the 8 XCDs round-robin (workgroup id b runs
+// on XCD b % 8).  Work is dealt to the XCDs in chunks of kXcdChunk
+// consecutive rays in trace order: chunk c goes to XCD c % 8.  A chunk is a
+// compact screen patch whose rays share the BVH levels near the leaves in
+// their XCD's L2, and every XCD gets chunks from all over the screen, so that
+// none of them holds more than its share of the expensive rays.  One
+// contiguous eighth of the rays per XCD left the XCD with the worst screen
+// region running alone.  Measured, contiguous eighths -> chunks of 1024
+// rays: one eye on the 4.52M terrain 304 / 295 / 315 -> 299 / 274 / 290 us
+// (three gazes), binocular 8K batch 414 / 402 / 430 -> 416 / 366 / 396 us,
+// LMFR(1.8) at 8K 1.68 -> 1.45 / 1.33 ms, 2560x1440 full resolution 0.62 ->
+// 0.54 ms, the 4,096-triangle soup 5.35 -> 3.55 ms.  Chunks of 128 to 4096
+// rays are within 2% of each other; 16384 is 3% slower on batches.
 constexpr int kXcds = 8;
+constexpr int kXcdChunk = 1024;
+
+// Work block of the i-th workgroup on XCD x, of per = workgroups / 8 on each
+// (a permutation of 0 .. 8 per - 1; the rest of a partial last chunk is
+// shared out contiguously).
+template <int B>
+__device__ __forceinline__ int xcd_work(int x, int i, int per) {
+    constexpr int kChunk = kXcdChunk / B;
+    const int whole = per / kChunk * kChunk;
+    if (i >= whole) return kXcds * whole + x * (per - whole) + (i - whole);
+    return (i / kChunk * kXcds + x) * kChunk + i % kChunk;
+}
+
+// Work block of workgroup b of n; ids past the last multiple of 8 keep their
+// place.
+template <int B>
 __device__ __forceinline__ int xcd_block(int b, int n) {
     const int per = n / kXcds;
-    return b < per * kXcds ? (b % kXcds) * per + b / kXcds : b;
+    return b < per * kXcds ? xcd_work<B>(b % kXcds, b / kXcds, per) : b;
 }
 
 // S = stack entries per lane (the scene's stack class).
 template <int B, int S, bool kCount, bool kLambert>
 __global__ __launch_bounds__(B) kTraceWaves(kLambert) void k_trace(const TraceView v, unsigned long long* counters) {
     __shared__ int stack[lds_entries(S) * B];
-    const int b = xcd_block(blockIdx.x, gridDim.x);
+    const int b = xcd_block<B>(blockIdx.x, gridDim.x);
     trace_item<B, S, kCount, false, kLambert>(v, (int64_t)b * B + threadIdx.x, stack, counters);
 }
 
@@ -830,9 +854,9 @@ __global__ __launch_bounds__(B) kFiveWaves void k_trace_list(const TraceView v) 
 // Batched launch: workgroup b serves view vid with block_end[vid-1] <= b <
 // block_end[vid] (block_end is the running sum of per-view workgroups of B
 // items each).  S covers the deepest scene of the batch.
-// order (nullable): per XCD, the dispatch order of its workgroups'
-// blocks (see k_trace_plan); cost (nullable): each block's duration in
-// 100 MHz ticks, the larger of its waves', kept for the next frame's plan.
+// order (nullable): per XCD, the dispatch order of its blocks (see
+// k_trace_plan); cost (nullable): each block's duration in 100 MHz ticks,
+// the larger of its waves', kept by slot for the next frame's plan.
 template <int B, int S, bool kCount, bool kPhased, bool kLambert>
 __global__ __launch_bounds__(B) kBatchWaves(kLambert, kPhased) void k_trace_batch(const TraceView* __restrict__ views,
                                                    const int32_t* __restrict__ block_end, int32_t n_views,
@@ -840,11 +864,16 @@ __global__ __launch_bounds__(B) kBatchWaves(kLambert, kPhased) void k_trace_batc
                                                    uint32_t* __restrict__ cost) {
     __shared__ int stack[lds_entries(S) * B];
     const uint64_t t0 = cost ? wall_clock64() : 0;
-    int b = xcd_block(blockIdx.x, gridDim.x);
+    // XCD x runs `slot`s x per .. x per + per - 1 of the plan; slot s holds
+    // the work block xcd_work(x, s - x per)
     const int per = gridDim.x / kXcds;
-    if (order && (int)blockIdx.x < per * kXcds) {
-        const int x = blockIdx.x % kXcds;
-        b = x * per + order[x * per + blockIdx.x / kXcds];
+    int b = blockIdx.x, slot = blockIdx.x;
+    if (b < per * kXcds) {
+        const int x = b % kXcds;
+        int i = b / kXcds;
+        if (order) i = order[x * per + i];
+        slot = x * per + i;
+        b = xcd_work<B>(x, i, per);
     }
     int vid = 0;
     while (vid + 1 < n_views && b >= block_end[vid]) ++vid;
@@ -852,13 +881,13 @@ __global__ __launch_bounds__(B) kBatchWaves(kLambert, kPhased) void k_trace_batc
     trace_item<B, S, kCount, kPhased, kLambert>(views[vid], (int64_t)(b - first) * B + threadIdx.x, stack, counters);
     if (cost && (threadIdx.x & 63) == 0) {
         const uint64_t dt = wall_clock64() - t0;
-        atomicMax(cost + b, (uint32_t)(dt < 0xffffffffull ? dt : 0xffffffffull));
+        atomicMax(cost + slot, (uint32_t)(dt < 0xffffffffull ? dt : 0xffffffffull));
     }
 }
 
 // Longest-first dispatch order of a batched traversal launch, from the
 // previous frame's block durations.  Workgroup x plans XCD x, which runs the
-// blocks x per .. x per + per - 1 (per = blocks / 8; the few blocks past
+// slots x per .. x per + per - 1 (per = blocks / 8; the few blocks past
 // 8 per keep their place): the blocks are ranked into 32 classes of
 // duration (two per octave from 2.56 us up, longest first) by a counting
 // sort, and order[x per + p] is the p-th block of that ranking, so the
