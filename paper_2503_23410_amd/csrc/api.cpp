@@ -317,6 +317,8 @@ extern "C" int vafr_scene_create(const float* xyz, int64_t n_verts, const int32_
         if (hipMalloc(&s->d_tris, tb) != hipSuccess) return cleanup(fail(VAFR_E_OOM, "hipMalloc of triangles"));
         if (nb && hipMemcpy(s->d_nodes, s->host.nodes.data(), nb, hipMemcpyHostToDevice) != hipSuccess)
             return cleanup(fail(VAFR_E_HIP, "upload of BVH nodes failed"));
+        if (int rc2 = format_nodes(s->d_nodes, (int64_t)s->host.nodes.size(), nullptr)) return cleanup(rc2);
+        if (hipStreamSynchronize(nullptr) != hipSuccess) return cleanup(fail(VAFR_E_HIP, "node formatting failed"));
         if (hipMemcpy(s->d_tris, s->host.tris.data(), tb, hipMemcpyHostToDevice) != hipSuccess)
             return cleanup(fail(VAFR_E_HIP, "upload of triangles failed"));
         s->device_bytes = (int64_t)(nb + tb);

@@ -365,13 +365,11 @@ int build_bvh(const float* xyz, int64_t n_verts, const int32_t* tri, int64_t n_t
     out->max_depth = b.max_depth.load();
     out->n_leaves = b.n_leaves.load();
     out->pad = 2e-5f * (1.0f + ext);
-    // fma(plane, 1/d, -o/d) moves a plane by at most 2^-24 |o|: keep that
-    // below pad / 8, and |o| small enough that o/d stays finite for the
-    // smallest substitute |d| of the traversal (1e-30).
-    // The quantised slab test forms fma(code, scale / d, (origin - o) / d);
-    // against the decoded plane its distance is that of a plane moved by at
-    // most 2^-24 (|o| + |origin - o| + |plane - o|) per axis, below pad / 8
-    // while every |o| component stays under pad 2^19 - ext.
+    // The traversal's fast slab test forms fma(code, scale / d, (origin - o) /
+    // d); against the exact distance to the stored plane its result is that
+    // of a plane moved by at most 2^-24 (|o| + |origin - o| + 2 |plane - o|)
+    // per axis, at most pad / 8 while every |o| component stays under
+    // pad 2^19 - ext.
     out->fma_origin_limit = std::max(0.0f, std::min(out->pad * 524288.0f - ext, 1.0e7f));
     Packer pk{xyz, tri, idx.data(), out->pad, out->stack + kStackSpill, out};
     out->nodes.reserve(out->n_leaves / 2 + 1);

@@ -177,7 +177,7 @@ struct TraceView {
     const float4* tris;
     int32_t root;
     int32_t stack;          // stack class of the scene (entries per lane)
-    float fma_origin_limit; // largest |origin| component for the FMA slab test
+    float fma_origin_limit; // largest |origin| component for the fast slab form
     // camera
     float eye[3], right[3], up[3], fwd[3];
     // film geometry (FP64): gaze point on the film and pixel pitch
@@ -225,6 +225,9 @@ struct TraceView {
     int32_t pt_phased;
 };
 
+// Turns uploaded nodes into the traversal's device format, in place (the
+// host's nodes keep the format of BvhNode).
+int format_nodes(BvhNode* nodes_dev, int64_t n, hipStream_t stream);
 // Work items of a view (padded to whole tiles for full-resolution / LMFR).
 int64_t trace_items_of(const TraceView& v);
 // Traversal workgroup sizes compiled in (one ray per thread).
