@@ -180,10 +180,18 @@ int describe(vafr_batch b, const vafr_view* views, int32_t n, int32_t* trace_blo
             ReconView r;
             if (int rc2 = make_recon_view(w.layout, w.gaze, w.lp_rgba_dev, w.img_rgba_dev, &r)) return rc2;
             if (!b->rv.empty() && pairable(b->rv.back(), r)) {
-                b->rv.back().lp2 = r.lp;
-                b->rv.back().img2 = r.img;
+                ReconView& first = b->rv.back();
+                rsum -= recon_blocks_of(first, b->cfg.recon_rows);
+                first.lp2 = r.lp;
+                first.img2 = r.img;
+                first.tall = 0;
+                rsum += recon_blocks_of(first, b->cfg.recon_rows);
+                if (rsum > 0x7fffffff) return fail(VAFR_E_UNSUPPORTED, "too many pixels in one batch");
+                b->rb.back() = (int32_t)rsum;
                 continue;
             }
+            // (until it pairs)
+            r.tall = r.mode == kModeVafr && b->cfg.recon_rows <= 4 && (int64_t)r.width * r.height >= kTallPixels;
             rsum += recon_blocks_of(r, b->cfg.recon_rows);
             if (rsum > 0x7fffffff) return fail(VAFR_E_UNSUPPORTED, "too many pixels in one batch");
             b->rv.push_back(r);

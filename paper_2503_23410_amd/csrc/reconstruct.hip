@@ -11,12 +11,20 @@
 // largest film radius of the tile and, in each column, the rows between the
 // smallest and the largest polar angle, with one texel of margin -- and the
 // workgroup copies those texels with row-contiguous loads; the four texels
-// of each pixel are then read from LDS.  A texel outside the staged region
-// (not expected, but the bound is computed in floating point) is read from
-// the LP buffer instead, so the result never depends on the bound.  Tiles
-// whose footprint exceeds the LDS budget -- those within a few degrees of
-// the gaze point, where one display pixel maps to about one texel or the
-// tile surrounds the gaze -- read every texel from the LP buffer.
+// of each pixel are then read from LDS.  In nearly every tile of a large
+// display the staged rows do not cross the seam: such tiles take sample_rows,
+// the others sample_vafr (178 VALU instructions per pixel), with the same
+// arithmetic.  A texel outside the
+// staged region (not expected, but the bound is computed in floating point)
+// is read from the LP buffer instead, so the result never depends on the
+// bound.  Tiles whose footprint exceeds the LDS budget -- those within a few
+// degrees of the gaze point, where one display pixel maps to about one texel
+// or the tile surrounds the gaze -- read every texel from the LP buffer.
+//
+// Measured, one view, all tiles in the general sampler -> now: 7680x4320 141 /
+// 127 -> 111 / 97 us (centred / off-centre gaze), 3840x2160 45 / 41 -> 38 / 34
+// us, 1921x1083 20 -> 15 us; binocular pairs at 8K 192 -> 180 us (6.1 TB/s, at
+// the rate of a store-only probe); 16 mixed views (unpaired) 1.22 -> 0.84 ms.
 //
 // A view may carry a second LP buffer and image with the same layout, gaze
 // and display (the other eye of a binocular frame): every pixel then reads
@@ -100,16 +108,31 @@ __device__ __forceinline__ float angle_turns(float dx, float dy) {
     return r;
 }
 
-// Rows j0, j1 = j0 + 1 (mod n) and weight t of angular interpolation in a
-// column of n rows, for turns in [0, 1]: s = turns n - 0.5 lies in
-// [-0.5, n - 0.5], so floor(s) is in [-1, n - 1] and only -1 wraps.
-__device__ __forceinline__ void column_rows(int n, float turns, int& j0, int& j1, float& t) {
-    const float s = fmaf(turns, (float)n, -0.5f);
+// Row floor(s) and weight t of angular interpolation in a column of n rows,
+// for turns in [0, 1]: s = turns n - 0.5 lies in [-0.5, n - 0.5].
+__device__ __forceinline__ int column_row(float n, float turns, float& t) {
+    const float s = fmaf(turns, n, -0.5f);
     const float fs = floorf(s);
     t = s - fs;
-    j0 = (int)fs;
+    return (int)fs;
+}
+
+// Rows j0, j1 = j0 + 1 (mod n): floor(s) is in [-1, n - 1], only -1 wraps.
+__device__ __forceinline__ void column_rows(int n, float turns, int& j0, int& j1, float& t) {
+    j0 = column_row((float)n, turns, t);
     j0 = j0 < 0 ? j0 + n : j0;
     j1 = j0 + 1 == n ? 0 : j0 + 1;
+}
+
+// Weights of the four texels of a pixel between two columns (w) and between
+// the two rows of each (t0, t1), every rounding stated: both samplers of a
+// tile give the same image whichever tiles take which.
+struct Weights {
+    float a, b, c, d;
+};
+__device__ __forceinline__ Weights tap_weights(float w, float t0, float t1) {
+    const float w0 = 1.0f - w;
+    return Weights{fmaf(-w0, t0, w0), w0 * t0, fmaf(-w, t1, w), w * t1};
 }
 
 // Weighted sum of four texels.
@@ -139,12 +162,19 @@ struct StageCol {
     uint32_t js_base;   // j_start | base << 16
 };
 
+// A staged column as sample_rows reads it: row j of its n rows, for js <= j
+// <= js + last + 1, at LDS byte at + 16 j.
+struct alignas(16) StageRow {
+    float n;
+    int at, js, last;
+};
+
 struct Stage {
     float4 tex[kStageTexels];
     StageCol col[kStageCols];
-    int base[kStageCols];   // first LDS texel of each staged column (ascending)
+    StageRow row[kStageCols + 1];   // the last column of the buffer is followed by itself
     int i_lo, n_cols;       // staged columns i_lo .. i_lo + n_cols - 1 (n_cols = 0: nothing staged)
-    int total;              // staged texels
+    int n_rows;             // entries of row[] (0: the tile takes the general sampler)
 };
 
 // Where texel j of the column described by (off, n, j_start, cnt, base)
@@ -211,14 +241,13 @@ __device__ __forceinline__ void sample_vafr(const ReconView& v, const Stage& st,
     column_rows(n1, turns, j10, j11, t1);
     const Tap ta = tap_of(off0, n0, js0, cnt0, base0, j00), tb = tap_of(off0, n0, js0, cnt0, base0, j01);
     const Tap tc = tap_of(off1, n1, js1, cnt1, base1, j10), td = tap_of(off1, n1, js1, cnt1, base1, j11);
-    const float w0 = 1.0f - w;
-    const float wa = w0 - w0 * t0, wb = w0 * t0, wc = w - w * t1, wd = w * t1;
-    c = blend4(texel(st, lp, 0, ta), wa, texel(st, lp, 0, tb), wb, texel(st, lp, 0, tc), wc, texel(st, lp, 0, td),
-               wd);
+    const Weights q = tap_weights(w, t0, t1);
+    c = blend4(texel(st, lp, 0, ta), q.a, texel(st, lp, 0, tb), q.b, texel(st, lp, 0, tc), q.c, texel(st, lp, 0, td),
+               q.d);
     if (kPair) {
         constexpr int h = kStageTexels / 2;
-        c2 = blend4(texel(st, lp2, h, ta), wa, texel(st, lp2, h, tb), wb, texel(st, lp2, h, tc), wc,
-                    texel(st, lp2, h, td), wd);
+        c2 = blend4(texel(st, lp2, h, ta), q.a, texel(st, lp2, h, tb), q.b, texel(st, lp2, h, tc), q.c,
+                    texel(st, lp2, h, td), q.d);
     }
 }
 
@@ -245,9 +274,15 @@ __device__ __forceinline__ float lafr_u(const ReconView& v, float z, double r2) 
     return (v.lf_bexp == 1.0f ? s : powf(s, v.lf_bexp)) * (1.0f - v.lf_uef) + v.lf_uef;
 }
 
+// Texel offsets (bytes) and weights of a pixel of an LMFR / LaFR view.
+struct DenseTaps {
+    uint32_t o00, o01, o10, o11;
+    float w, t;
+};
+
 // Pixel (x, y) of an LMFR / LaFR view: the offset from the gaze point is
 // formed in FP64 (the gaze is a continuous FP64 position), then rounded.
-__device__ __forceinline__ float4 sample_lmfr(const ReconView& v, __amdgpu_buffer_rsrc_t lp, int x, int y) {
+__device__ __forceinline__ DenseTaps dense_taps(const ReconView& v, int x, int y) {
     const double dxd = (double)x + v.lm_cx, dyd = (double)y + v.lm_cy;
     const float dx = (float)dxd, dy = (float)dyd;
     const double r2 = dxd * dxd + dyd * dyd;
@@ -260,14 +295,11 @@ __device__ __forceinline__ float4 sample_lmfr(const ReconView& v, __amdgpu_buffe
     int i0 = (int)a;
     i0 = i0 > v.n_cols - 1 ? v.n_cols - 1 : i0;
     const int i1 = i0 + 1 < v.n_cols ? i0 + 1 : v.n_cols - 1;
-    const float w = a - (float)i0;
     int j0, j1;
     float t;
     column_rows(v.lm_h, angle_turns(dx, dy), j0, j1, t);
     const uint32_t o0 = (uint32_t)(i0 * v.lm_h), o1 = (uint32_t)(i1 * v.lm_h);
-    const float w0 = 1.0f - w;
-    return blend4(ld4(lp, (o0 + j0) * 16u), w0 - w0 * t, ld4(lp, (o0 + j1) * 16u), w0 * t,
-                  ld4(lp, (o1 + j0) * 16u), w - w * t, ld4(lp, (o1 + j1) * 16u), w * t);
+    return DenseTaps{(o0 + j0) * 16u, (o0 + j1) * 16u, (o1 + j0) * 16u, (o1 + j1) * 16u, a - (float)i0, t};
 }
 
 // Wave 0: the staged columns of the tile whose pixel centres span film
@@ -276,7 +308,7 @@ __device__ __forceinline__ float4 sample_lmfr(const ReconView& v, __amdgpu_buffe
 __device__ void build_stage(const ReconView& v, Stage& st, __amdgpu_buffer_rsrc_t ut, __amdgpu_buffer_rsrc_t ct,
                             float xl, float xh, float yl, float yh, int budget) {
     const int lane = threadIdx.x;
-    int n_cols = 0, i_lo = 0, total = 0;
+    int n_cols = 0, i_lo = 0, n_rows = 0;
     const bool around_gaze = xl <= 0.0f && xh >= 0.0f && yl <= 0.0f && yh >= 0.0f;
     if (!around_gaze) {
         // radius range: nearest point of the rectangle and farthest corner
@@ -292,20 +324,23 @@ __device__ void build_stage(const ReconView& v, Stage& st, __amdgpu_buffer_rsrc_
         // angle range: the rectangle does not hold the gaze point, so the
         // extreme angles are those of its corners (taken about the centre
         // direction, which keeps the range unwrapped)
-        const float ref = angle_turns(0.5f * (xl + xh), 0.5f * (yl + yh));
-        float lo = 0.0f, hi = 0.0f;
-        const float cxs[4] = {xl, xh, xl, xh}, cys[4] = {yl, yl, yh, yh};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            float d = angle_turns(cxs[k], cys[k]) - ref;
-            d = d >= 0.5f ? d - 1.0f : (d < -0.5f ? d + 1.0f : d);
-            lo = fminf(lo, d);
-            hi = fmaxf(hi, d);
-        }
+        // Each lane takes one corner's angle from the centre's (the angle of
+        // (dot, cross), in [-1/2, 1/2] turns); groups of four lanes share
+        // the extremes.
+        const float rx = 0.5f * (xl + xh), ry = 0.5f * (yl + yh);
+        const float ref = angle_turns(rx, ry);
+        const float cx = lane & 1 ? xh : xl, cy = lane & 2 ? yh : yl;
+        float d = angle_turns(fmaf(cx, rx, cy * ry), fmaf(cy, rx, -(cx * ry)));
+        d = d >= 0.5f ? d - 1.0f : d;
+        float lo = fminf(d, 0.0f), hi = fmaxf(d, 0.0f);
+        lo = fminf(lo, __shfl_xor(lo, 1, 64));
+        hi = fmaxf(hi, __shfl_xor(hi, 1, 64));
+        lo = fminf(lo, __shfl_xor(lo, 2, 64));
+        hi = fmaxf(hi, __shfl_xor(hi, 2, 64));
         lo += ref;
         hi += ref;
         if (n_cols > kStageCols) n_cols = 0;
-        int cnt = 0, js = 0, n = 0;
+        int cnt = 0, js = 0, n = 0, j_first = 0;
         uint32_t off = 0;
         if (lane < n_cols) {
             const v2u c2 = ld2(ct, (uint32_t)(i_lo + lane) * 8u);
@@ -315,6 +350,7 @@ __device__ void build_stage(const ReconView& v, Stage& st, __amdgpu_buffer_rsrc_
             const int j_lo = (int)floorf(fmaf(lo, (float)n, -0.5f)) - 1;
             const int j_hi = (int)floorf(fmaf(hi, (float)n, -0.5f)) + 2;
             cnt = j_hi - j_lo + 1;
+            j_first = j_lo;
             if (cnt >= n) {
                 cnt = n;
                 js = 0;
@@ -323,75 +359,119 @@ __device__ void build_stage(const ReconView& v, Stage& st, __amdgpu_buffer_rsrc_
                 js = js < 0 ? js + n : js;
             }
         }
-        // exclusive prefix sum of the counts over the wave
+        // inclusive prefix sum of the counts over the wave, by row shifts
+        // within 16 lanes and broadcasts of lane 15 and lane 31
         int incl = cnt;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const int o = __shfl_up(incl, d, 64);
-            if (lane >= d) incl += o;
-        }
-        total = __shfl(incl, 63, 64);
+        incl += __builtin_amdgcn_update_dpp(0, incl, 0x111, 0xf, 0xf, true);    // row_shr:1
+        incl += __builtin_amdgcn_update_dpp(0, incl, 0x112, 0xf, 0xf, true);    // row_shr:2
+        incl += __builtin_amdgcn_update_dpp(0, incl, 0x114, 0xf, 0xf, true);    // row_shr:4
+        incl += __builtin_amdgcn_update_dpp(0, incl, 0x118, 0xf, 0xf, true);    // row_shr:8
+        incl += __builtin_amdgcn_update_dpp(0, incl, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
+        incl += __builtin_amdgcn_update_dpp(0, incl, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
+        const int total = __builtin_amdgcn_readlane(incl, 63);
         if (total > budget || __ballot(n_cols == 0) != 0) n_cols = 0;
-        if (n_cols == 0) total = 0;
+        // a tile whose rows would wrap round the seam takes the general sampler
+        const bool wraps = lane < n_cols && (j_first < 0 || j_first + cnt > n);
+        if (n_cols > 0 && __ballot(wraps) == 0) n_rows = n_cols;
         if (lane < n_cols) {
             StageCol sc;
             sc.off = off;
             sc.n_cnt = (uint32_t)n | ((uint32_t)cnt << 16);
             sc.js_base = (uint32_t)js | ((uint32_t)(incl - cnt) << 16);
             st.col[lane] = sc;
-            st.base[lane] = incl - cnt;
+            StageRow sr;
+            sr.n = (float)n;
+            sr.at = (incl - cnt - js) * 16;
+            sr.js = js;
+            sr.last = cnt - 2;
+            st.row[lane] = sr;
+            if (lane == n_cols - 1 && i_lo + n_cols == v.n_cols) st.row[n_cols] = sr;
         }
+        if (n_rows > 0 && i_lo + n_cols == v.n_cols) ++n_rows;
     }
     if (lane == 0) {
         st.i_lo = i_lo;
         st.n_cols = n_cols;
-        st.total = total;
+        st.n_rows = n_rows;
     }
 }
 
-// Staged texel k: its column (binary search over the column bases) and its
-// LP offset.
-__device__ __forceinline__ uint32_t stage_source(const Stage& st, int k) {
-    int lo = 0, hi = st.n_cols - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (st.base[mid] <= k) lo = mid;
-        else hi = mid - 1;
-    }
-    const StageCol sc = st.col[lo];
-    const int n = (int)(sc.n_cnt & 0xffffu), js = (int)(sc.js_base & 0xffffu);
-    int j = js + (k - st.base[lo]);
-    j = j >= n ? j - n : j;
-    return sc.off + (uint32_t)j;
-}
-
-// Thread t copies staged texels t, t + 256, ...: all of its loads are issued
-// before the first LDS write, so the copy costs one memory latency.  With
-// kPair (at most kStageTexels / 2 texels staged) the same texels of lp2 go
+// Half a wave copies one column at a time (a peripheral tile of an 8K display
+// has about ten columns of fourteen rows), its loads of up to four columns
+// issued before the first LDS write.  With kPair the same texels of lp2 go
 // to the upper half.
 template <bool kPair>
 __device__ __forceinline__ void fill_stage(Stage& st, __amdgpu_buffer_rsrc_t lp, __amdgpu_buffer_rsrc_t lp2) {
-    constexpr int kPer = (kPair ? kStageTexels / 2 : kStageTexels) / kReconThreads;
+    constexpr int kHalves = kReconThreads / 32, kAhead = kPair ? 2 : 4;
     constexpr int h = kStageTexels / 2;
-    const int total = st.total;
-    float4 t[kPer], t2[kPair ? kPer : 1];
+    const int half = threadIdx.x >> 5, r = threadIdx.x & 31;
+    const int n_cols = st.n_cols;
+    for (int c0 = half; c0 < n_cols; c0 += kHalves * kAhead) {
+        float4 t[kAhead], t2[kPair ? kAhead : 1];
+        int to[kAhead];
 #pragma unroll
-    for (int m = 0; m < kPer; ++m) {
-        const int k = threadIdx.x + m * kReconThreads;
-        if (k < total) {
-            const uint32_t src = stage_source(st, k) * 16u;
-            t[m] = ld4(lp, src);
-            if (kPair) t2[m] = ld4(lp2, src);
+        for (int q = 0; q < kAhead; ++q) {
+            const int c = c0 + q * kHalves;
+            to[q] = -1;
+            if (c < n_cols) {
+                const StageCol sc = st.col[c];
+                const int n = (int)(sc.n_cnt & 0xffffu), cnt = (int)(sc.n_cnt >> 16);
+                const int js = (int)(sc.js_base & 0xffffu), base = (int)(sc.js_base >> 16);
+                if (r < cnt) {
+                    int j = js + r;
+                    j = j >= n ? j - n : j;
+                    const uint32_t src = (sc.off + (uint32_t)j) * 16u;
+                    to[q] = base + r;
+                    t[q] = ld4(lp, src);
+                    if (kPair) t2[q] = ld4(lp2, src);
+                }
+                // longer columns (near the gaze) finish here
+                for (int k = r + 32; k < cnt; k += 32) {
+                    int j = js + k;
+                    j = j >= n ? j - n : j;
+                    const uint32_t src = (sc.off + (uint32_t)j) * 16u;
+                    st.tex[base + k] = ld4(lp, src);
+                    if (kPair) st.tex[h + base + k] = ld4(lp2, src);
+                }
+            }
         }
-    }
 #pragma unroll
-    for (int m = 0; m < kPer; ++m) {
-        const int k = threadIdx.x + m * kReconThreads;
-        if (k < total) {
-            st.tex[k] = t[m];
-            if (kPair) st.tex[h + k] = t2[m];
-        }
+        for (int q = 0; q < kAhead; ++q)
+            if (to[q] >= 0) {
+                st.tex[to[q]] = t[q];
+                if (kPair) st.tex[h + to[q]] = t2[q];
+            }
     }
+}
+
+// sample_vafr for a tile with StageRow records: the same coordinates and
+// weights, but the two rows of each column are neighbours in LDS, so a pixel
+// needs two addresses for its four texels and no wrap, clamp or fallback.
+// Returns false if a texel is not staged (not expected: the bound has a texel
+// of margin), for the caller to take the general sampler instead.
+template <bool kPair>
+__device__ __forceinline__ bool sample_rows(const Stage& st, int i_lo, int n_rows, float dx, float dy, float a,
+                                            float4& c, float4& c2) {
+    const int i0 = (int)a;
+    const float w = a - (float)i0;
+    const float turns = angle_turns(dx, dy);
+    const int k = i0 - i_lo;
+    bool staged = (unsigned)k < (unsigned)(n_rows - 1);
+    const StageRow* rec = st.row + (staged ? k : 0);
+    const StageRow s0 = rec[0], s1 = rec[1];
+    float t0, t1;
+    const int j0 = column_row(s0.n, turns, t0), j1 = column_row(s1.n, turns, t1);
+    staged = staged && (unsigned)(j0 - s0.js) <= (unsigned)s0.last && (unsigned)(j1 - s1.js) <= (unsigned)s1.last;
+    const char* base = reinterpret_cast<const char*>(st.tex);
+    const float4* p0 = reinterpret_cast<const float4*>(base + (staged ? s0.at + j0 * 16 : 0));
+    const float4* p1 = reinterpret_cast<const float4*>(base + (staged ? s1.at + j1 * 16 : 0));
+    const Weights q = tap_weights(w, t0, t1);
+    c = blend4(p0[0], q.a, p0[1], q.b, p1[0], q.c, p1[1], q.d);
+    if (kPair) {
+        constexpr int h = kStageTexels / 2;
+        c2 = blend4(p0[h], q.a, p0[h + 1], q.b, p1[h], q.c, p1[h + 1], q.d);
+    }
+    return staged;
 }
 
 // Tile `id` of view v: 64 x 4P pixels, P rows per wave.  M is the mapping
@@ -428,6 +508,7 @@ __device__ __forceinline__ void recon_tile(const ReconView& v, int id, Stage& st
         __syncthreads();
         if (x >= v.width) return;
         const float dx = fmaf((float)x, v.sx, v.cx);
+        const int i_lo = st.i_lo, n_rows = st.n_rows;
         // the radial table entries of all P pixels are loaded before the
         // first store, so their latencies overlap
         float tq[P];
@@ -446,17 +527,36 @@ __device__ __forceinline__ void recon_tile(const ReconView& v, int id, Stage& st
                 const float k = (float)(int)tq[r];
                 const float a = fmaf(tq[r] - k, __uint_as_float(uk[r].y), __uint_as_float(uk[r].x)) - 0.5f;
                 float4 c, c2;
-                sample_vafr<kPair>(v, st, lp, lp2, ct, dx, dy, a, c, c2);
+                bool done = false;
+                if (n_rows > 0) done = sample_rows<kPair>(st, i_lo, n_rows, dx, dy, a, c, c2);
+                if (!done) sample_vafr<kPair>(v, st, lp, lp2, ct, dx, dy, a, c, c2);
                 store_px(img, (uint32_t)(ty * v.width + x) * 16u, c);
                 if (kPair) store_px(img2, (uint32_t)(ty * v.width + x) * 16u, c2);
             }
         }
     } else {
         if (x >= v.width) return;
-        for (int r = 0; r < P; ++r) {
+        // two rows at a time: all eight loads are issued before the first use
+        constexpr int kRows = P < 2 ? 1 : 2;
+        for (int r = 0; r < P; r += kRows) {
             const int ty = wave * P + r;
-            if (ty >= rows) break;
-            store_px(img, (uint32_t)(ty * v.width + x) * 16u, sample_lmfr(v, lp, x, y0 + ty));
+            DenseTaps t[kRows];
+            float4 c[kRows][4];
+#pragma unroll
+            for (int q = 0; q < kRows; ++q) {
+                t[q] = dense_taps(v, x, y0 + ty + q);
+                c[q][0] = ld4(lp, t[q].o00);
+                c[q][1] = ld4(lp, t[q].o01);
+                c[q][2] = ld4(lp, t[q].o10);
+                c[q][3] = ld4(lp, t[q].o11);
+            }
+#pragma unroll
+            for (int q = 0; q < kRows; ++q) {
+                const float w = t[q].w, s = t[q].t, w0 = 1.0f - w;
+                if (ty + q < rows)
+                    store_px(img, (uint32_t)((ty + q) * v.width + x) * 16u,
+                             blend4(c[q][0], w0 - w0 * s, c[q][1], w0 * s, c[q][2], w - w * s, c[q][3], w * s));
+            }
         }
     }
 }
@@ -478,6 +578,7 @@ __global__ __launch_bounds__(kReconThreads) void k_recon_batch(const ReconView* 
     const int first = vid ? block_end[vid - 1] : 0;
     const ReconView& v = views[vid];
     if (v.lp2) recon_tile<P, kModeVafr, true>(v, b - first, st);
+    else if (P <= 4 && v.tall) recon_tile<2 * P, kModeVafr>(v, b - first, st);
     else recon_tile<P, -1>(v, b - first, st);
 }
 
@@ -486,11 +587,12 @@ __global__ __launch_bounds__(kReconThreads) void k_recon_batch(const ReconView* 
 bool recon_rows_ok(int rows) { return rows == 1 || rows == 2 || rows == 4 || rows == 8; }
 
 int64_t recon_blocks_of(const ReconView& v, int rows) {
-    const int tile_h = kWaves * rows;
+    const int tile_h = kWaves * rows * (v.tall ? 2 : 1);
     return (int64_t)((v.width + kTileW - 1) / kTileW) * ((v.height + tile_h - 1) / tile_h);
 }
 
 int launch_reconstruct(const ReconView& v, hipStream_t stream, int rows) {
+    if (rows == 0) rows = v.mode != kModeVafr ? kReconRowsDense : (int64_t)v.width * v.height < kTallPixels ? 4 : 8;
     if (!recon_rows_ok(rows)) return fail(VAFR_E_ARG, "reconstruction rows per thread must be 1, 2, 4 or 8");
     const int64_t blocks = recon_blocks_of(v, rows);
     if (blocks > 0x7fffffff) return fail(VAFR_E_UNSUPPORTED, "display too large");

@@ -297,16 +297,26 @@ struct ReconView {
     // display (the other eye), reconstructed in the same pass; or null
     const float4* lp2;
     float4* img2;
+    // batched frames: an unpaired VaFR view of a large display takes tiles of
+    // twice the batch's rows per thread
+    int32_t tall;
 };
 
 // Reconstruction workgroups have kReconThreads threads (4 waves); `rows` is
 // the number of display rows each thread writes, so a tile is 64 x 4 rows.
 constexpr int kReconThreads = 256;
 bool recon_rows_ok(int rows);
-constexpr int kReconRowsDefault = 8;        // per-view calls
 constexpr int kBatchReconRowsDefault = 4;   // batches: binocular pairs fit 64 VGPRs at 4 rows, not at 8
+// VaFR displays from this many pixels on are mapped 8 rows per thread, smaller
+// ones 4 (one view, rows 2 / 4 / 8: 1281x721 9.8 / 10.3 / 11.8 us, 1921x1083
+// 16 / 14 / 20 us, 3840x2160 35 / 30 / 35 us, 5120x2880 59 / 47 / 47 us,
+// 7680x4320 125 / 100 / 89 us): a small display needs the workgroups, a large
+// one the fewer tile set-ups.
+constexpr int64_t kTallPixels = 14000000;
+constexpr int kReconRowsDense = 2;          // LMFR / LaFR (8K: 141 us against 147 at 8 rows, 3839x2161: 34 against 43)
 int64_t recon_blocks_of(const ReconView& v, int rows);
-int launch_reconstruct(const ReconView& v, hipStream_t stream, int rows = kReconRowsDefault);
+// rows = 0: chosen by mapping and display size.
+int launch_reconstruct(const ReconView& v, hipStream_t stream, int rows = 0);
 int launch_reconstruct_batch(const ReconView* views_dev, const int32_t* block_end_dev, int32_t n_views,
                              int32_t blocks, int rows, hipStream_t stream);
 
