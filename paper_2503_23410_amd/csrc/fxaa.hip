@@ -13,9 +13,19 @@
 // built with -ffp-contract=off) are part of the library's contract with its
 // test oracle.
 //
-// One thread per texel.  The kernel reads the LP buffer through the caches
-// (17 MB per view): a texel and its direct neighbours come from the same or
-// adjacent columns, contiguous in the buffer for consecutive rows.
+// A workgroup takes a tile of kFxaaCols columns by one of the K equal sectors
+// that give each of those columns at most 64 rows, one column per wave, and
+// first copies the tile with the column on either side and three more rows at
+// either end into LDS.  Most texels compare within that window (an edge search
+// mostly ends after a step or two); what lies outside is read from the LP
+// buffer.  Straight from the LP buffer (one thread per texel, up to 24
+// dependent rounds of 16-byte gathers) the vector L1's return path was 70%
+// busy at three resident waves per SIMD: 48 us for the paper's layout on the
+// 4.52M terrain (nearly every texel an edge) and 29 us on the soup, now 35 and
+// 24 us; a buffer without edges takes 14 instead of 13 us.  What bounds it now
+// is the search: a wave walks on until the last of its 64 searches has ended.
+// Windows of 2 to 16 columns on either side and 4 to 10 rows, and tiles of 8,
+// 12 or 16 columns, measured 34-44 us.
 #include "vafr_internal.h"
 
 namespace vafr {
@@ -27,43 +37,68 @@ constexpr float kSubpix = 0.75f;     // weight of the sub-texel term
 constexpr int kSteps = 6;
 __constant__ float kStepAt[kSteps] = {1.0f, 2.0f, 3.0f, 4.0f, 6.0f, 8.0f};   // end-search offsets
 
+constexpr int kWindowCols = kFxaaCols + 16;       // the tile's columns and eight on either side
+constexpr int kHalo = 3;                           // rows staged past the tile's at either end
+constexpr int kWindowTexels = (kFxaaCols + 2) * (kFxaaRows + 2 * kHalo);
+
 struct FxaaView {
     const int2* col;     // (rows, first texel) per column
-    const int32_t* blk_col;   // column of the first texel of each workgroup
+    const int4* tile;    // (first column, sector, sectors, 0) per workgroup
     int32_t n_cols;
-    int64_t n_texels;
     const float4* in;
     float4* out;
 };
 
-// Row j (any integer, cyclic) of the column with record cn = (rows, first
-// texel); the modulo is only taken when j leaves [0, rows).
-__device__ __forceinline__ float4 texel_of(const FxaaView& v, int2 cn, int j) {
+// A column of the window: rows lo .. lo + pairs (cyclic: row j is row j mod
+// n) are at LDS texels base .. base + pairs; pairs = 0: none staged.
+struct WinCol {
+    int n, off, lo, base, pairs;
+};
+
+// The same record for every lane of the wave, in scalar registers.
+__device__ __forceinline__ WinCol uniform(const WinCol& w) {
+    return WinCol{__builtin_amdgcn_readfirstlane(w.n), __builtin_amdgcn_readfirstlane(w.off),
+                  __builtin_amdgcn_readfirstlane(w.lo), __builtin_amdgcn_readfirstlane(w.base),
+                  __builtin_amdgcn_readfirstlane(w.pairs)};
+}
+
+struct Window {
+    float4 tex[kWindowTexels];
+    WinCol col[kWindowCols];
+};
+
+// Row j (any integer, cyclic) of a column in the LP buffer; the modulo is
+// only taken when j leaves [0, rows).
+__device__ __forceinline__ float4 texel_of(const FxaaView& v, const WinCol& w, int j) {
     int r = j;
-    if ((unsigned)r >= (unsigned)cn.x) {
-        r = j % cn.x;
-        r = r < 0 ? r + cn.x : r;
+    if ((unsigned)r >= (unsigned)w.n) {
+        r = j % w.n;
+        r = r < 0 ? r + w.n : r;
     }
-    return v.in[(int64_t)cn.y + r];
+    return v.in[(int64_t)w.off + r];
 }
 
-__device__ __forceinline__ int clamp_col(const FxaaView& v, int c) {
-    return c < 0 ? 0 : (c >= v.n_cols ? v.n_cols - 1 : c);
+// Rows j and j + 1 of a column.
+__device__ __forceinline__ void texel_pair(const FxaaView& v, const Window& win, const WinCol& w, int j, float4& a,
+                                           float4& b) {
+    const int rel = j - w.lo;
+    if ((unsigned)rel < (unsigned)w.pairs) {
+        a = win.tex[w.base + rel];
+        b = win.tex[w.base + rel + 1];
+    } else {
+        a = texel_of(v, w, j);
+        b = texel_of(v, w, j + 1);
+    }
 }
 
-// The column with record cn at angle t turns, linear between rows.
-__device__ __forceinline__ float4 column_of(const FxaaView& v, int2 cn, float t) {
-    const float s = t * (float)cn.x - 0.5f;
+// The column at angle t turns, linear between rows.
+__device__ __forceinline__ float4 column_of(const FxaaView& v, const Window& win, const WinCol& cn, float t) {
+    const float s = t * (float)cn.n - 0.5f;
     const float fs = floorf(s);
     const float w = s - fs;
-    const int j0 = (int)fs;
-    const float4 a = texel_of(v, cn, j0), b = texel_of(v, cn, j0 + 1);
+    float4 a, b;
+    texel_pair(v, win, cn, (int)fs, a, b);
     return make_float4(a.x + w * (b.x - a.x), a.y + w * (b.y - a.y), a.z + w * (b.z - a.z), a.w + w * (b.w - a.w));
-}
-
-// Column c (clamped to the buffer) at angle t turns.
-__device__ __forceinline__ float4 column_at(const FxaaView& v, int c, float t) {
-    return column_of(v, v.col[clamp_col(v, c)], t);
 }
 
 __device__ __forceinline__ float luma(float4 p) { return (0.299f * p.x + 0.587f * p.y) + 0.114f * p.z; }
@@ -71,22 +106,29 @@ __device__ __forceinline__ float luma(float4 p) { return (0.299f * p.x + 0.587f 
 // |second difference| of three lumas along a line.
 __device__ __forceinline__ float curvature(float a, float m, float b) { return fabsf((a - m) + (b - m)); }
 
-__device__ float4 fxaa_texel(const FxaaView& v, int i, int j) {
+// Texel (i, j); first: the column of window entry 0.
+__device__ float4 fxaa_texel(const FxaaView& v, const Window& win, int first, int i, int j) {
+    auto window = [&](int c) -> const WinCol& {
+        c = c < 0 ? 0 : (c >= v.n_cols ? v.n_cols - 1 : c);
+        return win.col[c - first];
+    };
     // records of the texel's column and of its outer and inner neighbours
-    const int2 ci = v.col[i], co = v.col[clamp_col(v, i + 1)], cn = v.col[clamp_col(v, i - 1)];
-    const int n = ci.x;
+    const WinCol ci = uniform(window(i)), co = uniform(window(i + 1)), cn = uniform(window(i - 1));
+    const int n = ci.n;
     const float t = ((float)j + 0.5f) / (float)n;
     const float dt = 1.0f / (float)n;
-    const float4 M = texel_of(v, ci, j);
+    // (rows j - 1 .. j + 1 of a texel's own column are staged)
+    const float4* own = win.tex + ci.base + (j - ci.lo);
+    const float4 M = own[0];
     const float lM = luma(M);
-    const float lU = luma(texel_of(v, ci, j + 1)), lD = luma(texel_of(v, ci, j - 1));
-    const float lO = luma(column_of(v, co, t)), lI = luma(column_of(v, cn, t));
+    const float lU = luma(own[1]), lD = luma(own[-1]);
+    const float lO = luma(column_of(v, win, co, t)), lI = luma(column_of(v, win, cn, t));
     const float lmax = fmaxf(fmaxf(fmaxf(lM, lU), fmaxf(lD, lO)), lI);
     const float lmin = fminf(fminf(fminf(lM, lU), fminf(lD, lO)), lI);
     const float range = lmax - lmin;
     if (range < fmaxf(kEdgeMin, lmax * kEdgeRel)) return M;
-    const float lOU = luma(column_of(v, co, t + dt)), lOD = luma(column_of(v, co, t - dt));
-    const float lIU = luma(column_of(v, cn, t + dt)), lID = luma(column_of(v, cn, t - dt));
+    const float lOU = luma(column_of(v, win, co, t + dt)), lOD = luma(column_of(v, win, co, t - dt));
+    const float lIU = luma(column_of(v, win, cn, t + dt)), lID = luma(column_of(v, win, cn, t - dt));
     // luma curvature across the radius (three angles) and across the angle
     // (three radii), centre line weighted twice
     const float across_r = (curvature(lID, lD, lOD) + 2.0f * curvature(lI, lM, lO)) + curvature(lIU, lU, lOU);
@@ -98,7 +140,14 @@ __device__ float4 fxaa_texel(const FxaaView& v, int i, int j) {
     const float lSide = side > 0 ? lPos : lNeg;
     const float lLine = 0.5f * (lM + lSide);
     const float gScaled = 0.25f * fmaxf(gNeg, gPos);
+    // End search: step p (in the edge's direction) compares the mean luma of
+    // two samples with that of the edge's own two sides.  Along the angle
+    // they are (column i, its side's column) at angle t + p dt; along the
+    // radius, column i + p at angles t and t + side dt.  One form for both,
+    // chosen by selects: a wave holds edges of either kind.
     float dist[2], lEnd[2];
+    const int across = radial ? (side > 0 ? i + 1 : i - 1) : i;
+    const float t_side = radial ? t : t + (float)side * dt;
 #pragma unroll
     for (int dir = 0; dir < 2; ++dir) {
         const float sgn = dir == 0 ? -1.0f : 1.0f;
@@ -106,16 +155,10 @@ __device__ float4 fxaa_texel(const FxaaView& v, int i, int j) {
         lEnd[dir] = lLine;
         for (int k = 0; k < kSteps; ++k) {
             const float p = sgn * kStepAt[k];
-            float la, lb;
-            if (radial) {
-                const float tt = t + p * dt;
-                la = luma(column_of(v, ci, tt));
-                lb = luma(column_of(v, side > 0 ? co : cn, tt));
-            } else {
-                const int c = i + (int)p;
-                la = luma(column_at(v, c, t));
-                lb = luma(column_at(v, c, t + (float)side * dt));
-            }
+            const float tt = t + p * dt;
+            const int c = (int)p;
+            const float la = luma(column_of(v, win, window(radial ? i : i + c), radial ? tt : t));
+            const float lb = luma(column_of(v, win, window(radial ? across : i + c), radial ? tt : t_side));
             const float l = 0.5f * (la + lb);
             if (fabsf(l - lLine) >= gScaled) {
                 dist[dir] = kStepAt[k];
@@ -131,30 +174,89 @@ __device__ float4 fxaa_texel(const FxaaView& v, int i, int j) {
     const float s1 = fminf(fmaxf(fabsf(lAvg - lM) / range, 0.0f), 1.0f);
     const float s2 = (-2.0f * s1 + 3.0f) * (s1 * s1);
     const float off = fmaxf(edge, (s2 * s2) * kSubpix);
-    const float4 S = radial ? column_of(v, side > 0 ? co : cn, t) : texel_of(v, ci, j + side);
+    const float4 S = radial ? column_of(v, win, side > 0 ? co : cn, t) : own[side];
     return make_float4(M.x + off * (S.x - M.x), M.y + off * (S.y - M.y), M.z + off * (S.z - M.z),
                        M.w + off * (S.w - M.w));
 }
 
-__global__ __launch_bounds__(kTexelBlock) void k_fxaa(const FxaaView v) {
-    const int64_t k = (int64_t)blockIdx.x * kTexelBlock + threadIdx.x;
-    if (k >= v.n_texels) return;
-    // column of texel k: from the workgroup's first column, walk forward
-    // (a workgroup spans several columns only near the centre of the grid)
-    int c = v.blk_col[blockIdx.x];
-    while (c + 1 < v.n_cols && (int64_t)v.col[c + 1].y <= k) ++c;
-    v.out[k] = fxaa_texel(v, c, (int)(k - v.col[c].y));
+// First row of sector k of K in a column of n rows: the least j with
+// (j + 1/2) / n >= k / K.
+__device__ __forceinline__ int sector_row(int n, int k, int K) {
+    return (int)((2 * (int64_t)n * k + K - 1) / (2 * K));
+}
+
+__global__ __launch_bounds__(kFxaaThreads) void k_fxaa(const FxaaView v) {
+    __shared__ Window win;
+    const int4 tile = v.tile[blockIdx.x];
+    const int i0 = tile.x, k = tile.y, K = tile.z;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int i1 = min(i0 + kFxaaCols, v.n_cols);      // past the tile's last column
+    const int first = max(i0 - 8, 0), last = min(i1 + 8, v.n_cols);
+    if (wave == 0) {
+        WinCol w{1, 0, 0, 0, 0};
+        int cnt = 0;
+        if (lane < last - first) {
+            const int c = first + lane;
+            const int2 cn = v.col[c];
+            const int r0 = sector_row(cn.x, k, K), r1 = sector_row(cn.x, k + 1, K);
+            w.n = cn.x;
+            w.off = cn.y;
+            w.lo = r0 - kHalo;
+            // columns outside the tile can hold more rows of the sector than
+            // the tile's own: the rest of them is not staged
+            if (c >= i0 - 1 && c <= i1) cnt = min(r1 - r0, kFxaaRows) + 2 * kHalo;
+            w.pairs = cnt > 0 ? cnt - 1 : 0;
+        }
+        // exclusive prefix sum of the counts (at most 32 columns)
+        int incl = cnt;
+#pragma unroll
+        for (int d = 1; d < 32; d <<= 1) {
+            const int o = __shfl_up(incl, d, 64);
+            if (lane >= d) incl += o;
+        }
+        w.base = incl - cnt;
+        if (lane < last - first) win.col[lane] = w;
+    }
+    __syncthreads();
+    // a wave copies a column at a time, all of its loads before the first write
+    constexpr int kWaves = kFxaaThreads / 64, kMine = (kFxaaCols + 2 + kWaves - 1) / kWaves;
+    static_assert(kFxaaRows + 2 * kHalo <= 128, "two rows per lane");
+    const int s0 = max(i0 - 1, 0) - first, s1 = min(i1 + 1, v.n_cols) - first;
+    float4 t[kMine][2];
+#pragma unroll
+    for (int q = 0; q < kMine; ++q) {
+        const int c = s0 + wave + q * kWaves;
+        if (c < s1) {
+            const WinCol w = uniform(win.col[c]);
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                if (lane + 64 * h <= w.pairs) t[q][h] = texel_of(v, w, w.lo + lane + 64 * h);
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < kMine; ++q) {
+        const int c = s0 + wave + q * kWaves;
+        if (c < s1) {
+            const WinCol w = uniform(win.col[c]);
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                if (lane + 64 * h <= w.pairs) win.tex[w.base + lane + 64 * h] = t[q][h];
+        }
+    }
+    __syncthreads();
+    for (int i = i0 + wave; i < i1; i += kWaves) {
+        const WinCol w = uniform(win.col[i - first]);
+        const int r0 = w.lo + kHalo, rows = w.pairs + 1 - 2 * kHalo;
+        if (lane < rows) v.out[(int64_t)w.off + r0 + lane] = fxaa_texel(v, win, first, i, r0 + lane);
+    }
 }
 
 }  // namespace
 
-int launch_fxaa(const int2* col_dev, const int32_t* blk_col_dev, int32_t n_cols, int64_t n_texels, const float* in,
-                float* out, hipStream_t stream) {
-    if (n_texels <= 0) return VAFR_OK;
-    FxaaView v{col_dev, blk_col_dev, n_cols, n_texels, reinterpret_cast<const float4*>(in),
-               reinterpret_cast<float4*>(out)};
-    const int64_t blocks = (n_texels + kTexelBlock - 1) / kTexelBlock;
-    hipLaunchKernelGGL(k_fxaa, dim3((unsigned)blocks), dim3(kTexelBlock), 0, stream, v);
+int launch_fxaa(const LayoutDev& ld, int32_t n_cols, const float* in, float* out, hipStream_t stream) {
+    if (ld.n_fxaa_tiles <= 0) return VAFR_OK;
+    FxaaView v{ld.col, ld.fxaa_tile, n_cols, reinterpret_cast<const float4*>(in), reinterpret_cast<float4*>(out)};
+    hipLaunchKernelGGL(k_fxaa, dim3((unsigned)ld.n_fxaa_tiles), dim3(kFxaaThreads), 0, stream, v);
     VAFR_HIP(hipGetLastError());
     return VAFR_OK;
 }

@@ -158,27 +158,60 @@ int layout_device(vafr_layout L, const LayoutDev** out) {
     if (L->kind == VAFR_LAYOUT_VAFR) {
         std::vector<int2> col(L->n_cols);
         for (int i = 0; i < L->n_cols; ++i) col[i] = make_int2(L->n_rows[i], (int)L->col_off[i]);
-        VAFR_HIP(hipMalloc(&d.col, sizeof(int2) * col.size()));
-        VAFR_HIP(hipMemcpy(d.col, col.data(), sizeof(int2) * col.size(), hipMemcpyHostToDevice));
         std::vector<float2> dxy_ord(L->n_texels);
         for (int64_t k = 0; k < L->n_texels; ++k)
             dxy_ord[k] = make_float2(L->dxy[2 * (int64_t)L->ord[k]], L->dxy[2 * (int64_t)L->ord[k] + 1]);
-        VAFR_HIP(hipMalloc(&d.dxy, sizeof(float2) * dxy_ord.size()));
-        VAFR_HIP(hipMemcpy(d.dxy, dxy_ord.data(), sizeof(float2) * dxy_ord.size(), hipMemcpyHostToDevice));
-        VAFR_HIP(hipMalloc(&d.dxy_tex, sizeof(float) * L->dxy.size()));
-        VAFR_HIP(hipMemcpy(d.dxy_tex, L->dxy.data(), sizeof(float) * L->dxy.size(), hipMemcpyHostToDevice));
-        VAFR_HIP(hipMalloc(&d.ord, sizeof(int32_t) * L->ord.size()));
-        VAFR_HIP(hipMemcpy(d.ord, L->ord.data(), sizeof(int32_t) * L->ord.size(), hipMemcpyHostToDevice));
         std::vector<int32_t> blk((L->n_texels + kTexelBlock - 1) / kTexelBlock);
         for (int32_t c = 0, b = 0; b < (int32_t)blk.size(); ++b) {
             const int64_t k = (int64_t)b * kTexelBlock;
             while (c + 1 < L->n_cols && L->col_off[c + 1] <= k) ++c;
             blk[b] = c;
         }
-        VAFR_HIP(hipMalloc(&d.blk_col, sizeof(int32_t) * std::max<size_t>(1, blk.size())));
-        VAFR_HIP(hipMemcpy(d.blk_col, blk.data(), sizeof(int32_t) * blk.size(), hipMemcpyHostToDevice));
-        VAFR_HIP(hipMalloc(&d.u_of_rho, sizeof(float) * L->u_of_rho.size()));
-        VAFR_HIP(hipMemcpy(d.u_of_rho, L->u_of_rho.data(), sizeof(float) * L->u_of_rho.size(), hipMemcpyHostToDevice));
+        // anti-aliasing tiles: K sectors give every column of a group at most
+        // kFxaaRows rows
+        std::vector<int4> tile;
+        for (int32_t i = 0; i < L->n_cols; i += kFxaaCols) {
+            int32_t n = 1;
+            for (int32_t c = i; c < std::min(i + kFxaaCols, L->n_cols); ++c) n = std::max(n, L->n_rows[c]);
+            const int32_t sectors = (n + kFxaaRows - 1) / kFxaaRows;
+            for (int32_t k = 0; k < sectors; ++k) tile.push_back(make_int4(i, k, sectors, 0));
+        }
+        d.n_fxaa_tiles = (int32_t)tile.size();
+        // one allocation; the small tables go up in one copy
+        size_t bytes = 0;
+        auto place = [&](size_t n) {
+            const size_t at = bytes;
+            bytes += (n + 255) & ~(size_t)255;
+            return at;
+        };
+        const size_t at_col = place(sizeof(int2) * col.size()), at_blk = place(sizeof(int32_t) * blk.size());
+        const size_t at_tile = place(sizeof(int4) * tile.size()), at_u = place(sizeof(float) * L->u_of_rho.size());
+        std::vector<char> small(bytes);
+        std::memcpy(small.data() + at_col, col.data(), sizeof(int2) * col.size());
+        std::memcpy(small.data() + at_blk, blk.data(), sizeof(int32_t) * blk.size());
+        std::memcpy(small.data() + at_tile, tile.data(), sizeof(int4) * tile.size());
+        std::memcpy(small.data() + at_u, L->u_of_rho.data(), sizeof(float) * L->u_of_rho.size());
+        const size_t at_dxy = place(sizeof(float2) * dxy_ord.size()), at_tex = place(sizeof(float) * L->dxy.size());
+        const size_t at_ord = place(sizeof(int32_t) * L->ord.size());
+        VAFR_HIP(hipMalloc(&d.block, bytes));
+        hipError_t e = hipMemcpy(d.block, small.data(), small.size(), hipMemcpyHostToDevice);
+        if (e == hipSuccess)
+            e = hipMemcpy(d.block + at_dxy, dxy_ord.data(), sizeof(float2) * dxy_ord.size(), hipMemcpyHostToDevice);
+        if (e == hipSuccess)
+            e = hipMemcpy(d.block + at_tex, L->dxy.data(), sizeof(float) * L->dxy.size(), hipMemcpyHostToDevice);
+        if (e == hipSuccess)
+            e = hipMemcpy(d.block + at_ord, L->ord.data(), sizeof(int32_t) * L->ord.size(), hipMemcpyHostToDevice);
+        if (e != hipSuccess) {
+            (void)hipFree(d.block);
+            return hip_fail(e, "upload of layout tables");
+        }
+        d.col = reinterpret_cast<int2*>(d.block + at_col);
+        d.blk_col = reinterpret_cast<int32_t*>(d.block + at_blk);
+        d.fxaa_tile = reinterpret_cast<int4*>(d.block + at_tile);
+        d.u_of_rho = reinterpret_cast<float2*>(d.block + at_u);
+        d.dxy = reinterpret_cast<float2*>(d.block + at_dxy);
+        d.dxy_tex = reinterpret_cast<float2*>(d.block + at_tex);
+        d.ord = reinterpret_cast<int32_t*>(d.block + at_ord);
     } else {
         std::vector<double2> cs(L->max_rows);
         for (int j = 0; j < L->max_rows; ++j) cs[j] = make_double2(L->lm_cos[j], L->lm_sin[j]);
@@ -418,12 +451,7 @@ extern "C" void vafr_layout_destroy(vafr_layout L) {
     bool have = hipGetDevice(&cur) == hipSuccess;
     for (auto& d : L->dev) {
         if (hipSetDevice(d.device) != hipSuccess) continue;
-        (void)hipFree(d.col);
-        (void)hipFree(d.dxy);
-        (void)hipFree(d.dxy_tex);
-        (void)hipFree(d.ord);
-        (void)hipFree(d.blk_col);
-        (void)hipFree(d.u_of_rho);
+        (void)hipFree(d.block);
         (void)hipFree(d.lm_z);
         (void)hipFree(d.lm_cs);
     }

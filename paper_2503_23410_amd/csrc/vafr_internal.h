@@ -41,11 +41,14 @@ constexpr int kURhoN = 16384;
 // Per-device copy of a layout's tables.
 struct LayoutDev {
     int device = -1;
+    char* block = nullptr;        // VaFR: the allocation that holds the tables below
     int2* col = nullptr;          // VaFR: (n_rows, col_off) per column
     float2* dxy = nullptr;        // VaFR: film offset per texel, in trace order
     float2* dxy_tex = nullptr;    // VaFR: film offset per texel, in texel order
     int32_t* ord = nullptr;       // VaFR: texel index of each trace-order slot
     int32_t* blk_col = nullptr;   // VaFR: column of texel 256 b (per-texel kernels' block start)
+    int4* fxaa_tile = nullptr;    // VaFR: tiles of the LP anti-aliasing (first column, sector, sectors, 0)
+    int32_t n_fxaa_tiles = 0;
     float2* u_of_rho = nullptr;   // VaFR: (u_k, u_{k+1} - u_k) at rho_k = k h, k <= kURhoN
     double* lm_z = nullptr;       // LMFR: z_i per column
     double2* lm_cs = nullptr;     // LMFR: (cos, sin) of theta_j per row
@@ -341,11 +344,11 @@ struct RepBuffers {
 int launch_rep(const LayoutDev& ld, const vafr_layout_s& L, double gx, double gy, const vafr_camera& right,
                const RepBuffers& b, hipStream_t stream);
 
-// LP anti-aliasing over all texels of a VaFR layout (col: per-column rows
-// and first texel on the device).
 constexpr int kTexelBlock = 256;   // texels per workgroup of per-texel kernels
-int launch_fxaa(const int2* col_dev, const int32_t* blk_col_dev, int32_t n_cols, int64_t n_texels, const float* in,
-                float* out, hipStream_t stream);
+// LP anti-aliasing over all texels of a VaFR layout, in tiles of kFxaaCols
+// columns by a sector of at most kFxaaRows rows of each.
+constexpr int kFxaaCols = 4, kFxaaRows = 64, kFxaaThreads = 256;
+int launch_fxaa(const LayoutDev& ld, int32_t n_cols, const float* in, float* out, hipStream_t stream);
 
 // vafr_shade_lp_rep on a given workspace (validation included); the
 // allocation-free entry point passes its static scratch array.
