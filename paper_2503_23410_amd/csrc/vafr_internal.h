@@ -235,10 +235,16 @@ int format_nodes(BvhNode* nodes_dev, int64_t n, hipStream_t stream);
 int64_t trace_items_of(const TraceView& v);
 // Traversal workgroup sizes compiled in (one ray per thread).
 bool trace_block_ok(int block);
-constexpr int kTraceBlockDefault = 128;
+constexpr int kTraceBlockDefault = 128;   // batches
+// Per-view launches end with a tail of single long waves, and a workgroup
+// keeps its slots until its last wave ends: one-wave workgroups measured 259 /
+// 235 / 251 us per eye on the 4.52M terrain against 267 / 242 / 252 of two
+// waves (256 rays: 273 / 244 / 259), 2560x1440 full resolution 435 against 450
+// us (472), LMFR(1.8) at 8K 1.21 against 1.25 ms (1.30).
+constexpr int kTraceBlockSingle = 64;
 // counters != nullptr selects the diagnostic work-counting pass.
 int launch_trace(const TraceView& v, hipStream_t stream, unsigned long long* counters = nullptr,
-                 int block = kTraceBlockDefault);
+                 int block = kTraceBlockSingle);
 // One launch over several views: workgroup b serves the view whose running
 // workgroup count block_end[] first exceeds b.
 // stack = the largest stack class among the views' scenes; phased: some view
