@@ -79,6 +79,8 @@ static int scene_into_view(vafr_scene s, TraceView* v) {
     v->root = s->host.root;
     v->stack = s->host.stack;
     v->fma_origin_limit = s->host.fma_origin_limit;
+    std::memcpy(v->lo, s->host.lo, sizeof(v->lo));
+    std::memcpy(v->hi, s->host.hi, sizeof(v->hi));
     return VAFR_OK;
 }
 

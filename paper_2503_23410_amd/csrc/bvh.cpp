@@ -371,6 +371,10 @@ int build_bvh(const float* xyz, int64_t n_verts, const int32_t* tri, int64_t n_t
     // per axis, at most pad / 8 while every |o| component stays under
     // pad 2^19 - ext.
     out->fma_origin_limit = std::max(0.0f, std::min(out->pad * 524288.0f - ext, 1.0e7f));
+    for (int k = 0; k < 3; ++k) {
+        out->lo[k] = Packer::down((double)root->box.lo[k] - out->pad);
+        out->hi[k] = Packer::up((double)root->box.hi[k] + out->pad);
+    }
     Packer pk{xyz, tri, idx.data(), out->pad, out->stack + kStackSpill, out};
     out->nodes.reserve(out->n_leaves / 2 + 1);
     out->tris.reserve(3 * n_tris);

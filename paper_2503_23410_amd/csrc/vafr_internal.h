@@ -146,6 +146,7 @@ struct HostBvh {
     int32_t max_stack = 0;       // most stack entries a traversal can hold
     int32_t stack = kStackShort; // traversal stack class (kStackShort or kStackLong)
     float pad = 0.0f;            // absolute padding of every stored box
+    float lo[3] = {}, hi[3] = {};    // the scene's padded box
     float fma_origin_limit = 0;  // origins up to this |component| move a slab plane by <= pad / 8 (fast form)
     int64_t n_leaves = 0;
 };
@@ -181,6 +182,7 @@ struct TraceView {
     int32_t root;
     int32_t stack;          // stack class of the scene (entries per lane)
     float fma_origin_limit; // largest |origin| component for the fast slab form
+    float lo[3], hi[3];     // the scene's padded box
     // camera
     float eye[3], right[3], up[3], fwd[3];
     // film geometry (FP64): gaze point on the film and pixel pitch

@@ -78,3 +78,30 @@ def test_axis_parallel_rays(O, light):
     assert ok.mean() > 0.99
     assert np.array_equal(hid.cpu().numpy()[ok], ids[ok])
     assert np.abs(img.cpu().numpy() - rgba)[ok].max() <= 2e-3
+
+
+# The reprojection's list of uncovered texels: a left eye that looks away from
+# the scene hits nothing, so nothing is warped, every texel of the right eye is
+# listed and must equal the directly shaded one.  Short lists (four lanes per Lambert-shaded ray, whose
+# way is cut into segments), long ones, and path-traced ones; the far eyes see
+# the scene's box from outside, from afar and not at all.
+@pytest.mark.parametrize("e_max", [0.1, 3.0, 60.0])
+@pytest.mark.parametrize("mode", ["lambert", "unshadowed", "path"])
+@pytest.mark.parametrize("eye", [(0.1, 0.2, 0.3), (0.0, 0.0, 40.0), (3.0e4, 10.0, 2.0e4)])
+def test_listed_texels_equal_the_shaded_ones(e_max, mode, eye):
+    import torch
+    from paper_2503_23410_amd import vafr as V
+    scene = V.Scene(*I.soup_scene(2000, seed=8))
+    L = V.Layout.vafr(V.display(640, 360), [0.0, 10.0, 20.0, 30.0, 60.0], [40.0, 10.0, 6.0, 5.0, 4.0], e_max)
+    left = np.array([0, 0, -3, -1, 0, 0, 0, 1, 0, 0, 0, -1], np.float32)
+    right = np.array([*eye, -1, 0, 0, 0, 1, 0, 0, 0, -1], np.float32)
+    gaze = V.gaze(300.0, 170.0)
+    sh = V.shading(mode=V.VAFR_SHADE_PATH, bounces=1, seed=3) if mode == "path" else V.shading(shadow=mode == "lambert")
+    lp = [torch.full((L.n_texels, 4), float("nan"), device="cuda") for _ in range(3)]
+    ids = [torch.full((L.n_texels,), -7, device="cuda", dtype=torch.int32) for _ in range(3)]
+    ws = torch.empty(V.rep_workspace_bytes(L), device="cuda", dtype=torch.uint8)
+    V.vafr_shade_lp_rep(scene, V.camera(left), V.camera(right), gaze, sh, L, lp[0], lp[1], ws, ids[0], ids[1])
+    V.vafr_shade_lp(scene, V.camera(right), gaze, sh, L, lp[2], ids[2])
+    torch.cuda.synchronize()
+    assert torch.equal(ids[1], ids[2])
+    assert torch.equal(lp[1], lp[2])
