@@ -96,6 +96,20 @@ static void fill_view_common(TraceView& v, const vafr_camera* cam, const vafr_sh
     v.light_dir[0] = (float)(lx / len);
     v.light_dir[1] = (float)(ly / len);
     v.light_dir[2] = (float)(lz / len);
+    {
+        const float* d = v.light_dir;
+        for (int k = 0; k < 3; ++k)
+            v.light_inv[k] = 1.0f / (std::fabs(d[k]) < kFastTiny ? std::copysign(kFastTiny, d[k]) : d[k]);
+        int kz = 0;
+        if (std::fabs(d[1]) > std::fabs(d[kz])) kz = 1;
+        if (std::fabs(d[2]) > std::fabs(d[kz])) kz = 2;
+        int kx = (kz + 1) % 3, ky = (kz + 2) % 3;
+        if (d[kz] < 0.0f) std::swap(kx, ky);
+        v.light_shear[0] = d[kx] / d[kz];
+        v.light_shear[1] = d[ky] / d[kz];
+        v.light_shear[2] = 1.0f / d[kz];
+        v.light_axes = kx | ky << 2 | kz << 4;
+    }
     std::memcpy(v.light_rgb, sh->light_rgb, sizeof(v.light_rgb));
     std::memcpy(v.ambient, sh->ambient, sizeof(v.ambient));
     std::memcpy(v.background, sh->background, sizeof(v.background));

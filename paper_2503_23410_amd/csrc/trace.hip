@@ -23,11 +23,10 @@ constexpr float kHitSlack = 1.00001f;
 constexpr float kTiny = 1e-30f;
 // The fast slab form works on distances scaled by 2^-100 (see node_slabs).
 // It takes rays whose largest direction component lies in [kFastDirLo,
-// kFastDirHi], and raises components below kFastTiny to it: over the
+// kFastDirHi], and raises components below kFastTiny (2^-57) to it: over the
 // distances it admits, that moves a ray by less than 2^-27 of the padding.
 constexpr float kDistScale = 0x1p-100f;
 constexpr float kCodeScale = 0x1p49f;    // 2^149 kDistScale: a code read as the bits of a float is code x 2^-149
-constexpr float kFastTiny = 0x1p-57f;
 constexpr float kFastDirLo = 0x1p-10f, kFastDirHi = 0x1p20f;
 
 // Scene arrays are read through global-address-space pointers: the loads
@@ -101,6 +100,30 @@ __device__ __forceinline__ void ray_setup(float ox, float oy, float oz, float dx
     r.Sx = dkx / dkz;
     r.Sy = dky / dkz;
     r.Sz = 1.0f / dkz;
+}
+
+// The view's shadow ray from o: ray_setup along the light direction, whose
+// part that does not depend on the origin the host prepared (six divisions,
+// about 1% of a wave's issue cycles).
+__device__ __forceinline__ void light_ray(const TraceView& v, const float3 o, RayPre& r) {
+    r.ox = o.x; r.oy = o.y; r.oz = o.z;
+    r.dx = v.light_dir[0]; r.dy = v.light_dir[1]; r.dz = v.light_dir[2];
+    r.ix = v.light_inv[0]; r.iy = v.light_inv[1]; r.iz = v.light_inv[2];
+    r.oix = o.x * r.ix * kDistScale;
+    r.oiy = o.y * r.iy * kDistScale;
+    r.oiz = o.z * r.iz * kDistScale;
+    r.mx = (uint32_t)((int)__float_as_uint(r.ix) >> 31);
+    r.my = (uint32_t)((int)__float_as_uint(r.iy) >> 31);
+    r.mz = (uint32_t)((int)__float_as_uint(r.iz) >> 31);
+    r.kx = v.light_axes & 3; r.ky = (v.light_axes >> 2) & 3; r.kz = v.light_axes >> 4;
+    r.Sx = v.light_shear[0]; r.Sy = v.light_shear[1]; r.Sz = v.light_shear[2];
+    r.valid = true;
+    // Kept in vector registers: with a scalar operand a 2-cycle instruction
+    // takes 4 (v_fma 0.36 against 0.22 per SIMD and clock).  Left as scalars
+    // these constants made one eye on the 4.52M terrain 270 instead of 263 us
+    // and LMFR(1.8) at 8K 1.27 instead of 1.22 ms.
+    __asm__("" : "+v"(r.ix), "+v"(r.iy), "+v"(r.iz), "+v"(r.Sx), "+v"(r.Sy), "+v"(r.Sz));
+    __asm__("" : "+v"(r.mx), "+v"(r.my), "+v"(r.mz), "+v"(r.kx), "+v"(r.ky), "+v"(r.kz));
 }
 
 // Component of (a0, a1, a2) on axis K when K is fixed at compile time, else
@@ -622,6 +645,7 @@ __device__ __forceinline__ void film_ray(const TraceView& v, double Px, double P
         d[k] = (float)(s + (double)v.fwd[k]);
     }
     ray_setup(v.eye[0], v.eye[1], v.eye[2], d[0], d[1], d[2], r);
+    __asm__("" : "+v"(r.ox), "+v"(r.oy), "+v"(r.oz));   // not as scalar operands, see light_ray
 }
 
 // LaFR (Sec. 4.1 Eq. (15)) column -> log ratio z, inverting the kernel piece
@@ -706,7 +730,7 @@ __device__ float4 shade_lambert(const TraceView& v, RayPre& r, int64_t& out, int
     float vis = 1.0f;
     if (ndl > 0.0f && v.shadow) {
         RayPre s;
-        ray_setup(os.x, os.y, os.z, v.light_dir[0], v.light_dir[1], v.light_dir[2], s);
+        light_ray(v, os, s);
         ++n_shadow;
         if (any_hit<B, S, kCount, kPerm>(sc, s, stk, wc)) vis = 0.0f;
     }
@@ -746,7 +770,7 @@ __device__ bool path_segment(const TraceView& v, RayPre& r, uint32_t texel, int*
         float vis = 0.0f;
         if (ndl > 0.0f) {
             RayPre s;
-            ray_setup(os.x, os.y, os.z, v.light_dir[0], v.light_dir[1], v.light_dir[2], s);
+            light_ray(v, os, s);
             ++n_shadow;
             vis = any_hit<B, S, kCount>(sc, s, stk, wc) ? 0.0f : 1.0f;
         }
@@ -850,7 +874,7 @@ __device__ bool path_bounce(const TraceView& v, RayPre& r, int32_t p, int32_t ou
     state_fence();
     if (ndl > 0.0f) {
         RayPre s;
-        ray_setup(os.x, os.y, os.z, v.light_dir[0], v.light_dir[1], v.light_dir[2], s);
+        light_ray(v, os, s);
         vis = any_hit<B, S, false, true>(v, s, stk, wc) ? 0.0f : 1.0f;
     }
     state_fence();
@@ -1054,7 +1078,7 @@ __device__ void trace_item_split(const TraceView& v, int64_t k, int c, int* stk)
         float vis = 1.0f;
         if (ndl > 0.0f && v.shadow) {
             RayPre s;
-            ray_setup(os.x, os.y, os.z, v.light_dir[0], v.light_dir[1], v.light_dir[2], s);
+            light_ray(v, os, s);
             float ts;
             int ids;
             int any = traverse<B, S, true, false, true, true>(v, s, stk, ts, ids, wc, ray_segment(v, s, c)) >= 0;

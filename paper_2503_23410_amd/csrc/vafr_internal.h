@@ -168,6 +168,8 @@ struct vafr_scene_s {
 namespace vafr {
 
 // ------------------------------------------------------------ trace kernels
+// Direction components below this count as this in the fast slab test.
+constexpr float kFastTiny = 0x1p-57f;
 enum RayMode : int32_t { kModeVafr = 0, kModeLmfr = 1, kModeFull = 2 };
 
 // Everything one view's rays need; passed by value (kernel argument) or
@@ -203,6 +205,11 @@ struct TraceView {
     double lf_fa, lf_uef, lf_sexp, lf_zef_inv, lf_k;
     // shading
     float light_dir[3], light_rgb[3], ambient[3], background[3];
+    // set-up of a ray along light_dir (ray_setup's values, formed on the host
+    // with the same IEEE operations): reciprocals, shear constants, axes kx |
+    // ky << 2 | kz << 4
+    float light_inv[3], light_shear[3];
+    int32_t light_axes;
     int32_t shadow;
     int32_t bounces;
     uint32_t seed_lo, seed_hi, frame, view;
