@@ -95,7 +95,8 @@ int layout_device(vafr_layout L, const LayoutDev** out);
 
 // -------------------------------------------------------------------- BVH
 // Device node: up to four child boxes, quantised, and four references
-// (64 bytes; the traversal is bound by the bytes its lanes load).
+// (64 bytes; the traversal is bound by VALU issue and by the bytes its lanes
+// load).
 //   org  = (origin.x, origin.y, origin.z, scale.z): the node's box corner
 //          and the z scale;
 //   q0   = (lo.x, hi.x, lo.y, hi.y), q1 = (lo.z, hi.z, scale.x, scale.y):
@@ -104,6 +105,8 @@ int layout_device(vafr_layout L, const LayoutDev** out);
 //   ref  = the four child references.
 // Every decoded plane, computed as fmaf(code, scale, origin), lies outside
 // the child's padded FP32 box (the builder checks each one).
+// On the device (after format_nodes) origins are stored times 2^-100 and
+// scales times 2^49, for the traversal's fast slab form.
 // ref >= 0: internal node index; ref == kEmptyRef: no child (skipped by its
 // reference); otherwise a leaf, ~ref = first << 3 | (count-1).
 struct alignas(16) BvhNode {
