@@ -370,7 +370,7 @@ typedef struct {
  * display rows each reconstruction thread writes (1, 2, 4 or 8; a
  * workgroup of 256 threads covers 64 x 4 recon_rows pixels; VaFR views of
  * large displays that share no workgroups with another eye take twice the
- * rows, up to 8) and whether frames are replayed from a hipGraph. */
+ * rows, up to 8, and two eyes of smaller displays half of 4 or 8) and whether frames are replayed from a hipGraph. */
 typedef struct {
     int32_t trace_block;
     int32_t recon_rows;

@@ -184,14 +184,14 @@ int describe(vafr_batch b, const vafr_view* views, int32_t n, int32_t* trace_blo
                 rsum -= recon_blocks_of(first, b->cfg.recon_rows);
                 first.lp2 = r.lp;
                 first.img2 = r.img;
-                first.tall = 0;
+                first.rows_shift = b->cfg.recon_rows >= 4 && (int64_t)r.width * r.height < kTallPixels ? -1 : 0;
                 rsum += recon_blocks_of(first, b->cfg.recon_rows);
                 if (rsum > 0x7fffffff) return fail(VAFR_E_UNSUPPORTED, "too many pixels in one batch");
                 b->rb.back() = (int32_t)rsum;
                 continue;
             }
             // (until it pairs)
-            r.tall = r.mode == kModeVafr && b->cfg.recon_rows <= 4 && (int64_t)r.width * r.height >= kTallPixels;
+            r.rows_shift = r.mode == kModeVafr && b->cfg.recon_rows <= 4 && (int64_t)r.width * r.height >= kTallPixels;
             rsum += recon_blocks_of(r, b->cfg.recon_rows);
             if (rsum > 0x7fffffff) return fail(VAFR_E_UNSUPPORTED, "too many pixels in one batch");
             b->rv.push_back(r);

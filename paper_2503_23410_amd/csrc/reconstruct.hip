@@ -577,8 +577,9 @@ __global__ __launch_bounds__(kReconThreads) void k_recon_batch(const ReconView* 
     while (vid + 1 < n_views && b >= block_end[vid]) ++vid;
     const int first = vid ? block_end[vid - 1] : 0;
     const ReconView& v = views[vid];
-    if (v.lp2) recon_tile<P, kModeVafr, true>(v, b - first, st);
-    else if (P <= 4 && v.tall) recon_tile<2 * P, kModeVafr>(v, b - first, st);
+    if (v.lp2 && P >= 4 && v.rows_shift < 0) recon_tile<(P + 1) / 2, kModeVafr, true>(v, b - first, st);
+    else if (v.lp2) recon_tile<P, kModeVafr, true>(v, b - first, st);
+    else if (P <= 4 && v.rows_shift > 0) recon_tile<2 * P, kModeVafr>(v, b - first, st);
     else recon_tile<P, -1>(v, b - first, st);
 }
 
@@ -587,7 +588,7 @@ __global__ __launch_bounds__(kReconThreads) void k_recon_batch(const ReconView* 
 bool recon_rows_ok(int rows) { return rows == 1 || rows == 2 || rows == 4 || rows == 8; }
 
 int64_t recon_blocks_of(const ReconView& v, int rows) {
-    const int tile_h = kWaves * rows * (v.tall ? 2 : 1);
+    const int tile_h = kWaves * (v.rows_shift < 0 ? rows / 2 : rows << v.rows_shift);
     return (int64_t)((v.width + kTileW - 1) / kTileW) * ((v.height + tile_h - 1) / tile_h);
 }
 

@@ -319,8 +319,9 @@ struct ReconView {
     const float4* lp2;
     float4* img2;
     // batched frames: an unpaired VaFR view of a large display takes tiles of
-    // twice the batch's rows per thread
-    int32_t tall;
+    // twice the batch's rows per thread (1; rows <= 4), a pair of smaller
+    // displays half of them (-1; rows >= 4)
+    int32_t rows_shift;
 };
 
 // Reconstruction workgroups have kReconThreads threads (4 waves); `rows` is
@@ -334,6 +335,10 @@ constexpr int kBatchReconRowsDefault = 4;   // batches: binocular pairs fit 64 V
 // 7680x4320 125 / 100 / 89 us): a small display needs the workgroups, a large
 // one the fewer tile set-ups.
 constexpr int64_t kTallPixels = 14000000;
+// Binocular pairs in batches of 4 or 8 rows halve them below the same size (one
+// pair, rows 8 / 4 / 2: 640x360 26 / 17.5 / 13.9 us, 2560x1440 43 / 36 / 33 us,
+// 3840x2160 70 / 60 / 57 us, but 5120x2880 91 / 83 / 88 us and 7680x4320 185 /
+// 177 / 173 - 185 us from one card to the next).
 constexpr int kReconRowsDense = 2;          // LMFR / LaFR (8K: 141 us against 147 at 8 rows, 3839x2161: 34 against 43)
 int64_t recon_blocks_of(const ReconView& v, int rows);
 // rows = 0: chosen by mapping and display size.

@@ -1,6 +1,7 @@
 """Tile shapes of the VaFR inverse map (GPU): the display size where views
 change from 4 to 8 rows per thread, and batched unpaired views of large
-displays, whose tiles are twice as tall."""
+displays, whose tiles are twice as tall, and pairs of smaller ones, whose
+tiles are half as tall."""
 import numpy as np
 import pytest
 
@@ -62,5 +63,28 @@ def test_unpaired_large_view_in_a_batch(rows):
     for k, s in enumerate(sizes):
         one = torch.empty_like(img[k])
         V.vafr_reconstruct(L[s], gaze[k], lp[k], one)
+        torch.cuda.synchronize()
+        assert torch.equal(one, img[k]), k
+
+
+# either side of 14,000,000 pixels; tiles with one row of pixels left; tiny ones
+@pytest.mark.parametrize("W,H", [(3741, 3742), (3742, 3742), (65, 33), (130, 65), (64, 7), (3, 1)])
+@pytest.mark.parametrize("rows", [1, 2, 4, 8])
+def test_pairs_at_tile_edges(W, H, rows):
+    """Two pairs of a display give the images of the per-view calls, bit for
+    bit."""
+    import torch
+    from paper_2503_23410_amd import vafr as V
+    scene = V.Scene(*I.soup_scene(40, seed=2))
+    cams = [V.camera(c) for c in (I.soup_camera(), I.soup_camera() + np.float32(0.01))]
+    sh, L = V.shading(), V.Layout.vafr(V.display(W, H))
+    gaze = [V.gaze(0.6 * W, 0.4 * H)] * 2 + [V.gaze(-3.0, 0.5 * H)] * 2
+    lp = [torch.empty((L.n_texels, 4), device="cuda") for _ in gaze]
+    img = [torch.full((W * H, 4), float("nan"), device="cuda") for _ in gaze]
+    V.Batch(4, recon_rows=rows).run([V.view(V.VAFR_VIEW_VAFR, scene, cams[k % 2], g, sh, layout=L, lp_rgba=lp[k],
+                                            img_rgba=img[k]) for k, g in enumerate(gaze)])
+    for k, g in enumerate(gaze):
+        one = torch.empty_like(img[k])
+        V.vafr_reconstruct(L, g, lp[k], one)
         torch.cuda.synchronize()
         assert torch.equal(one, img[k]), k
