@@ -592,27 +592,14 @@ int64_t recon_blocks_of(const ReconView& v, int rows) {
     return (int64_t)((v.width + kTileW - 1) / kTileW) * ((v.height + tile_h - 1) / tile_h);
 }
 
-int launch_reconstruct(const ReconView& v, hipStream_t stream, int rows) {
-    if (rows == 0) rows = v.mode != kModeVafr ? kReconRowsDense : (int64_t)v.width * v.height < kTallPixels ? 4 : 8;
-    if (!recon_rows_ok(rows)) return fail(VAFR_E_ARG, "reconstruction rows per thread must be 1, 2, 4 or 8");
+int launch_reconstruct(const ReconView& v, hipStream_t stream) {
+    const int rows = v.mode != kModeVafr ? kReconRowsDense : (int64_t)v.width * v.height < kTallPixels ? 4 : 8;
     const int64_t blocks = recon_blocks_of(v, rows);
     if (blocks > 0x7fffffff) return fail(VAFR_E_UNSUPPORTED, "display too large");
     const dim3 g((unsigned)blocks), t(kReconThreads);
-    if (v.mode == kModeVafr) {
-        switch (rows) {
-            case 1: hipLaunchKernelGGL((k_recon<1, kModeVafr>), g, t, 0, stream, v); break;
-            case 2: hipLaunchKernelGGL((k_recon<2, kModeVafr>), g, t, 0, stream, v); break;
-            case 4: hipLaunchKernelGGL((k_recon<4, kModeVafr>), g, t, 0, stream, v); break;
-            default: hipLaunchKernelGGL((k_recon<8, kModeVafr>), g, t, 0, stream, v); break;
-        }
-    } else {
-        switch (rows) {
-            case 1: hipLaunchKernelGGL((k_recon<1, kModeLmfr>), g, t, 0, stream, v); break;
-            case 2: hipLaunchKernelGGL((k_recon<2, kModeLmfr>), g, t, 0, stream, v); break;
-            case 4: hipLaunchKernelGGL((k_recon<4, kModeLmfr>), g, t, 0, stream, v); break;
-            default: hipLaunchKernelGGL((k_recon<8, kModeLmfr>), g, t, 0, stream, v); break;
-        }
-    }
+    if (v.mode != kModeVafr) hipLaunchKernelGGL((k_recon<kReconRowsDense, kModeLmfr>), g, t, 0, stream, v);
+    else if (rows == 4) hipLaunchKernelGGL((k_recon<4, kModeVafr>), g, t, 0, stream, v);
+    else hipLaunchKernelGGL((k_recon<8, kModeVafr>), g, t, 0, stream, v);
     VAFR_HIP(hipGetLastError());
     return VAFR_OK;
 }

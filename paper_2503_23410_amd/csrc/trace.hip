@@ -1193,8 +1193,9 @@ __global__ __launch_bounds__(kPlanThreads) void k_trace_plan(uint32_t* __restric
     }
 }
 
-template <int B, int S>
+template <int S>
 void launch_single(const TraceView& v, int64_t blocks, hipStream_t stream, unsigned long long* counters) {
+    constexpr int B = kTraceBlockSingle;
     if (v.item_list)
         hipLaunchKernelGGL((k_trace_list<B, S>), dim3((unsigned)std::min<int64_t>(kSplit * blocks, kListBlocks)), dim3(B), 0,
                            stream, v);
@@ -1219,14 +1220,6 @@ void launch_batch(const TraceView* views, const int32_t* block_end, int32_t n_vi
     else
         hipLaunchKernelGGL((k_trace_batch<B, S, false, false, true>), dim3((unsigned)blocks), dim3(B), 0, stream,
                            views, block_end, n_views, counters, order, cost);
-}
-
-template <int S>
-void launch_single_s(const TraceView& v, int64_t blocks, int block, hipStream_t stream,
-                     unsigned long long* counters) {
-    if (block == 64) launch_single<64, S>(v, blocks, stream, counters);
-    else if (block == 128) launch_single<128, S>(v, blocks, stream, counters);
-    else launch_single<256, S>(v, blocks, stream, counters);
 }
 
 template <int S>
@@ -1273,15 +1266,14 @@ int64_t trace_items_of(const TraceView& v) {
 
 bool trace_block_ok(int block) { return block == 64 || block == 128 || block == 256; }
 
-int launch_trace(const TraceView& v, hipStream_t stream, unsigned long long* counters, int block) {
+int launch_trace(const TraceView& v, hipStream_t stream, unsigned long long* counters) {
     if (v.n_items <= 0) return VAFR_OK;
-    if (!trace_block_ok(block)) return fail(VAFR_E_ARG, "trace workgroup size must be 64, 128 or 256");
     if (!stack_ok(v.stack)) return fail(VAFR_E_ARG, "unknown traversal stack class %d", v.stack);
-    const int64_t blocks = (v.n_items + block - 1) / block;
+    const int64_t blocks = (v.n_items + kTraceBlockSingle - 1) / kTraceBlockSingle;
     if (v.item_list && counters) return fail(VAFR_E_UNSUPPORTED, "work counting does not take an item list");
     if (blocks > 0x7fffffff) return fail(VAFR_E_UNSUPPORTED, "too many rays in one launch");
-    if (v.stack == kStackShort) launch_single_s<kStackShort>(v, blocks, block, stream, counters);
-    else launch_single_s<kStackLong>(v, blocks, block, stream, counters);
+    if (v.stack == kStackShort) launch_single<kStackShort>(v, blocks, stream, counters);
+    else launch_single<kStackLong>(v, blocks, stream, counters);
     VAFR_HIP(hipGetLastError());
     return VAFR_OK;
 }

@@ -255,8 +255,7 @@ constexpr int kTraceBlockDefault = 128;   // batches
 // us (472), LMFR(1.8) at 8K 1.21 against 1.25 ms (1.30).
 constexpr int kTraceBlockSingle = 64;
 // counters != nullptr selects the diagnostic work-counting pass.
-int launch_trace(const TraceView& v, hipStream_t stream, unsigned long long* counters = nullptr,
-                 int block = kTraceBlockSingle);
+int launch_trace(const TraceView& v, hipStream_t stream, unsigned long long* counters = nullptr);
 // One launch over several views: workgroup b serves the view whose running
 // workgroup count block_end[] first exceeds b.
 // stack = the largest stack class among the views' scenes; phased: some view
@@ -341,8 +340,8 @@ constexpr int64_t kTallPixels = 14000000;
 // 177 / 173 - 185 us from one card to the next).
 constexpr int kReconRowsDense = 2;          // LMFR / LaFR (8K: 141 us against 147 at 8 rows, 3839x2161: 34 against 43)
 int64_t recon_blocks_of(const ReconView& v, int rows);
-// rows = 0: chosen by mapping and display size.
-int launch_reconstruct(const ReconView& v, hipStream_t stream, int rows = 0);
+// Rows per thread chosen by mapping and display size.
+int launch_reconstruct(const ReconView& v, hipStream_t stream);
 int launch_reconstruct_batch(const ReconView* views_dev, const int32_t* block_end_dev, int32_t n_views,
                              int32_t blocks, int rows, hipStream_t stream);
 
