@@ -393,8 +393,9 @@ __device__ __forceinline__ void leaf_step(int perm, const TraceView& sc, const R
 // kPerm, perm is the rays' axis permutation (perm_code) when every lane of
 // the wave shares it, else -1.  With kSeg the ray is followed over distances
 // [seg.x, seg.y] only: every box that meets that range is visited, so a hit
-// within it is found; hits outside it may be.
-template <int B, int S, bool kAny, bool kCount, bool kFast, bool kPerm, bool kSeg>
+// within it is found; hits outside it may be.  The first kBase entries of
+// each lane's LDS column are left alone (they hold what waits for the result).
+template <int B, int S, bool kAny, bool kCount, bool kFast, bool kPerm, bool kSeg, int kBase>
 __device__ int traverse_loop(const TraceView& sc, const RayPre& r, int* stk, float& t_best, int& id_best,
                              WorkCount& wc, int perm, float2 seg) {
     t_best = INFINITY;
@@ -404,18 +405,18 @@ __device__ int traverse_loop(const TraceView& sc, const RayPre& r, int* stk, flo
     // case stays an LDS access and the rare one a scratch access, neither a
     // generic one; volatile keeps the spill area in memory instead of in
     // registers).  The position is kept as the LDS byte offset of the next
-    // free entry; entry 0 holds kEmptyRef, so a pop needs no empty check.
+    // free entry; the first holds kEmptyRef, so a pop needs no empty check.
     // Whether any lane is near the end of its LDS column is checked once per
     // node step, for the whole wave.
     constexpr int kLds = lds_entries(S);
     constexpr uint32_t kStep = 4u * B, kLdsEnd = kStep * kLds;
-    int spill_mem[S + kStackSpill - kLds + 1];
+    int spill_mem[S + kStackSpill - kLds + kBase + 1];
     volatile __attribute__((address_space(5))) int* spill =
         (volatile __attribute__((address_space(5))) int*)spill_mem;
     auto lds = [&](uint32_t o) -> __attribute__((address_space(3))) int& {
         return *(__attribute__((address_space(3))) int*)((__attribute__((address_space(3))) char*)(stk) + o);
     };
-    uint32_t sp = 4u * threadIdx.x;
+    uint32_t sp = 4u * threadIdx.x + kBase * kStep;
     auto push = [&](bool checked, int v) {
         if (!checked || sp < kLdsEnd) lds(sp) = v;
         else spill[(sp - kLdsEnd) / kStep] = v;
@@ -535,7 +536,7 @@ __device__ int traverse_loop(const TraceView& sc, const RayPre& r, int* stk, flo
 // small screen patch).  The phased path kernels take it for their shadow
 // rays only: bounce rays rarely share a permutation, and fixing it for
 // every traversal there cost more in registers than it saved.
-template <int B, int S, bool kAny, bool kCount, bool kPerm, bool kSeg = false>
+template <int B, int S, bool kAny, bool kCount, bool kPerm, bool kSeg = false, int kBase = 0>
 __device__ __forceinline__ int traverse(const TraceView& sc, const RayPre& r, int* stk, float& t_best, int& id_best,
                                         WorkCount& wc, float2 seg = make_float2(0.0f, INFINITY)) {
     const float om = fmaxf(fmaxf(fabsf(r.ox), fabsf(r.oy)), fabsf(r.oz));
@@ -548,18 +549,18 @@ __device__ __forceinline__ int traverse(const TraceView& sc, const RayPre& r, in
         perm = __ballot(pc != p0) == 0 ? p0 : -1;
     }
     if (__ballot(!fast) == 0)
-        return traverse_loop<B, S, kAny, kCount, true, kPerm, kSeg>(sc, r, stk, t_best, id_best, wc, perm, seg);
+        return traverse_loop<B, S, kAny, kCount, true, kPerm, kSeg, kBase>(sc, r, stk, t_best, id_best, wc, perm, seg);
     RayPre g = r;
     g.ix = 1.0f / (r.dx == 0.0f ? copysignf(kTiny, r.dx) : r.dx);
     g.iy = 1.0f / (r.dy == 0.0f ? copysignf(kTiny, r.dy) : r.dy);
     g.iz = 1.0f / (r.dz == 0.0f ? copysignf(kTiny, r.dz) : r.dz);
-    return traverse_loop<B, S, kAny, kCount, false, kPerm, kSeg>(sc, g, stk, t_best, id_best, wc, perm, seg);
+    return traverse_loop<B, S, kAny, kCount, false, kPerm, kSeg, kBase>(sc, g, stk, t_best, id_best, wc, perm, seg);
 }
 
-template <int B, int S, bool kCount, bool kPerm = false>
+template <int B, int S, bool kCount, bool kPerm = false, int kBase = 0>
 __device__ __forceinline__ int closest_hit(const TraceView& sc, const RayPre& r, int* stk, float& t_best,
                                            int& id_best, WorkCount& wc) {
-    return traverse<B, S, false, kCount, kPerm>(sc, r, stk, t_best, id_best, wc);
+    return traverse<B, S, false, kCount, kPerm, false, kBase>(sc, r, stk, t_best, id_best, wc);
 }
 
 template <int B, int S, bool kCount, bool kPerm = false>
@@ -698,27 +699,53 @@ __device__ __forceinline__ bool make_item_ray(const TraceView& v, int64_t k, Ray
     return true;
 }
 
-template <int B, int S, bool kCount, bool kPerm>
+// While the primary ray is traced its direction and output slot (below 2^32:
+// no buffer has more than 65536 x 65536 items) wait outside the registers,
+// which lets the Lambert-only kernels run eight waves per SIMD.  kSolo
+// (per-view launches): in four entries at the bottom of the lane's LDS
+// column, found again from the lane's number.  In scratch, where batches keep
+// them, each wave pays a trip to memory that only a launch of many waves
+// hides: 4,347 rays on the 17,664-triangle terrain took 15.8 us (12.9 with
+// everything in registers at seven waves) and take 13.0, a 1280x720 view that
+// sees nothing 16.8 (12.1) and 14.2, one eye of 1.06M rays on the 1.13M
+// terrain 206 and 202, LMFR(1.8) at 8K 1.057 and 1.027 ms.  In LDS the
+// batched kernel spills six registers inside its loop (binocular frame on the
+// 4.52M terrain 346 -> 360 us).
+template <int B, int S, bool kCount, bool kPerm, bool kSolo>
 __device__ float4 shade_lambert(const TraceView& v, RayPre& r, int64_t& out, int* stk, int& id_out, WorkCount& wc,
                                 uint32_t& n_shadow, float4& p_out) {
     const TraceView& sc = v;
     float t;
-    // the direction and the output slot wait in scratch while the primary
-    // ray is traced: five registers that let the Lambert-only kernels run
-    // eight waves per SIMD
-    int keep_mem[5];
-    volatile __attribute__((address_space(5))) int* keep = (volatile __attribute__((address_space(5))) int*)keep_mem;
-    keep[0] = __float_as_int(r.dx);
-    keep[1] = __float_as_int(r.dy);
-    keep[2] = __float_as_int(r.dz);
-    keep[3] = (int)(uint32_t)out;
-    keep[4] = (int)(out >> 32);
-    int id;
-    const int slot = closest_hit<B, S, kCount, kPerm>(sc, r, stk, t, id, wc);
-    r.dx = __int_as_float(keep[0]);
-    r.dy = __int_as_float(keep[1]);
-    r.dz = __int_as_float(keep[2]);
-    out = (int64_t)keep[4] << 32 | (uint32_t)keep[3];
+    int id, slot;
+    if constexpr (kSolo) {
+        static_assert(B == 64, "one wave: a lane's column is its number");
+        volatile __attribute__((address_space(3))) int* keep = (volatile __attribute__((address_space(3))) int*)stk;
+        const uint32_t at = threadIdx.x;
+        keep[at] = __float_as_int(r.dx);
+        keep[at + B] = __float_as_int(r.dy);
+        keep[at + 2 * B] = __float_as_int(r.dz);
+        keep[at + 3 * B] = (int)(uint32_t)out;
+        slot = closest_hit<B, S, kCount, kPerm, 4>(sc, r, stk, t, id, wc);
+        uint32_t lane;   // (formed here, not kept from above)
+        __asm__ volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
+        r.dx = __int_as_float(keep[lane]);
+        r.dy = __int_as_float(keep[lane + B]);
+        r.dz = __int_as_float(keep[lane + 2 * B]);
+        out = (uint32_t)keep[lane + 3 * B];
+    } else {
+        int keep_mem[5];
+        volatile __attribute__((address_space(5))) int* keep = (volatile __attribute__((address_space(5))) int*)keep_mem;
+        keep[0] = __float_as_int(r.dx);
+        keep[1] = __float_as_int(r.dy);
+        keep[2] = __float_as_int(r.dz);
+        keep[3] = (int)(uint32_t)out;
+        keep[4] = (int)(out >> 32);
+        slot = closest_hit<B, S, kCount, kPerm>(sc, r, stk, t, id, wc);
+        r.dx = __int_as_float(keep[0]);
+        r.dy = __int_as_float(keep[1]);
+        r.dz = __int_as_float(keep[2]);
+        out = (int64_t)keep[4] << 32 | (uint32_t)keep[3];
+    }
     id_out = id;
     p_out = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     if (slot < 0) return make_float4(v.background[0], v.background[1], v.background[2], 1.0f);
@@ -892,8 +919,9 @@ __device__ bool path_bounce(const TraceView& v, RayPre& r, int32_t p, int32_t ou
 // triangle tests, and writes no image.  kPhased: path-mode views of the
 // launch run their bounce 0 as the first phase of path_bounce (batched
 // launches only).  kLambert: every view of the launch is Lambert-shaded, so
-// the path-tracing code is left out of the kernel.
-template <int B, int S, bool kCount, bool kPhased = false, bool kLambert = false>
+// the path-tracing code is left out of the kernel.  kSolo: the launch has one
+// view.
+template <int B, int S, bool kCount, bool kPhased = false, bool kLambert = false, bool kSolo = false>
 __device__ __forceinline__ void trace_item(const TraceView& v, int64_t k, int* stack, unsigned long long* counters) {
     RayPre r;
     int64_t out;
@@ -919,7 +947,7 @@ __device__ __forceinline__ void trace_item(const TraceView& v, int64_t k, int* s
     if (!kLambert && !kPhased && v.shade_mode == VAFR_SHADE_PATH)
         c = shade_path<B, S, kCount>(v, r, (uint32_t)out, stk, id, wc, n_shadow, p);
     else
-        c = shade_lambert<B, S, kCount, kLambert>(v, r, out, stk, id, wc, n_shadow, p);
+        c = shade_lambert<B, S, kCount, kLambert, kSolo>(v, r, out, stk, id, wc, n_shadow, p);
     if (kCount) {
         atomicAdd(counters + 0, 1ull);
         atomicAdd(counters + 1, (unsigned long long)n_shadow);
@@ -937,7 +965,7 @@ __device__ __forceinline__ void trace_item(const TraceView& v, int64_t k, int* s
 // whole paths in one pass (per-view path mode, the reprojection's list)
 // keep five waves (at most 96 VGPRs): below that their extra state spills.
 // The Lambert-only kernels, which keep the primary ray's direction and
-// output slot in scratch while it is traced, and the phased path-mode
+// output slot elsewhere while it is traced, and the phased path-mode
 // kernels, which hold no path state across a traversal, take the eight-wave
 // budget (64 VGPRs); at the 69 VGPRs the former take otherwise, a
 // 2560x1440 full-resolution view on the 1.13M terrain takes 0.50 ms instead
@@ -986,7 +1014,7 @@ template <int B, int S, bool kCount, bool kLambert>
 __global__ __launch_bounds__(B) kTraceWaves(kLambert) void k_trace(const TraceView v, unsigned long long* counters) {
     __shared__ int stack[lds_entries(S) * B];
     const int b = xcd_block<B>(blockIdx.x, gridDim.x);
-    trace_item<B, S, kCount, false, kLambert>(v, (int64_t)b * B + threadIdx.x, stack, counters);
+    trace_item<B, S, kCount, false, kLambert, kLambert>(v, (int64_t)b * B + threadIdx.x, stack, counters);
 }
 
 // Bounce `bounce` > kPathFuse of the phased path-mode views (batched): workgroup b
