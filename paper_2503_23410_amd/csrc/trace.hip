@@ -395,7 +395,7 @@ __device__ __forceinline__ void leaf_step(int perm, const TraceView& sc, const R
 // [seg.x, seg.y] only: every box that meets that range is visited, so a hit
 // within it is found; hits outside it may be.  The first kBase entries of
 // each lane's LDS column are left alone (they hold what waits for the result).
-template <int B, int S, bool kAny, bool kCount, bool kFast, bool kPerm, bool kSeg, int kBase>
+template <int B, int S, bool kAny, bool kCount, bool kFast, bool kPerm, bool kSeg, int kBase, bool kUni>
 __device__ int traverse_loop(const TraceView& sc, const RayPre& r, int* stk, float& t_best, int& id_best,
                              WorkCount& wc, int perm, float2 seg) {
     t_best = INFINITY;
@@ -453,13 +453,19 @@ __device__ int traverse_loop(const TraceView& sc, const RayPre& r, int* stk, flo
                 float tn[4];
                 uint32_t miss[4];
                 int4 rf;
-                // a node that every active lane visits (35-46% of the node
-                // steps of coherent rays) comes through the scalar cache,
-                // which spares the vector path four 16-byte loads per lane:
-                // 2.60 -> 2.53 ms for a batch of 16 views on the 4.52M
-                // terrain, 1.38 -> 1.34 ms per path-traced binocular frame
+                // kUni: a node that every active lane visits (35-46% of the
+                // node steps of coherent rays) comes through the scalar
+                // cache, which spares the vector path four 16-byte loads per
+                // lane.  That pays where many waves keep the vector path
+                // full: 2.60 -> 2.53 ms for a batch of 16 views on the 4.52M
+                // terrain, 1.38 -> 1.34 ms per path-traced binocular frame.
+                // A per-view launch waits for its longest waves instead, and
+                // a scalar load is a wave's longer wait: without it 83 -> 80
+                // us (283 thousand rays on the 1.13M terrain), 202 -> 198 us
+                // (1.06M), 256 -> 250 us (LMFR, 2561x1441), 1.027 -> 1.010 ms
+                // (LMFR(1.8), 8K), and 1% either way on the soup.
                 const int ref0 = __builtin_amdgcn_readfirstlane(ref);
-                if (__ballot(ref != ref0) == 0) {
+                if (kUni && __ballot(ref != ref0) == 0) {
                     const BvhNode n = scalar_node(sc.nodes, ref0);
                     rf = n.ref;
                     node_slabs<kFast, kAny, kSeg>(r, n.org, n.q0, n.q1, rf, tlim, seg.x, tn, miss);
@@ -536,7 +542,7 @@ __device__ int traverse_loop(const TraceView& sc, const RayPre& r, int* stk, flo
 // small screen patch).  The phased path kernels take it for their shadow
 // rays only: bounce rays rarely share a permutation, and fixing it for
 // every traversal there cost more in registers than it saved.
-template <int B, int S, bool kAny, bool kCount, bool kPerm, bool kSeg = false, int kBase = 0>
+template <int B, int S, bool kAny, bool kCount, bool kPerm, bool kSeg = false, int kBase = 0, bool kUni = true>
 __device__ __forceinline__ int traverse(const TraceView& sc, const RayPre& r, int* stk, float& t_best, int& id_best,
                                         WorkCount& wc, float2 seg = make_float2(0.0f, INFINITY)) {
     const float om = fmaxf(fmaxf(fabsf(r.ox), fabsf(r.oy)), fabsf(r.oz));
@@ -549,25 +555,26 @@ __device__ __forceinline__ int traverse(const TraceView& sc, const RayPre& r, in
         perm = __ballot(pc != p0) == 0 ? p0 : -1;
     }
     if (__ballot(!fast) == 0)
-        return traverse_loop<B, S, kAny, kCount, true, kPerm, kSeg, kBase>(sc, r, stk, t_best, id_best, wc, perm, seg);
+        return traverse_loop<B, S, kAny, kCount, true, kPerm, kSeg, kBase, kUni>(sc, r, stk, t_best, id_best, wc, perm,
+                                                                                 seg);
     RayPre g = r;
     g.ix = 1.0f / (r.dx == 0.0f ? copysignf(kTiny, r.dx) : r.dx);
     g.iy = 1.0f / (r.dy == 0.0f ? copysignf(kTiny, r.dy) : r.dy);
     g.iz = 1.0f / (r.dz == 0.0f ? copysignf(kTiny, r.dz) : r.dz);
-    return traverse_loop<B, S, kAny, kCount, false, kPerm, kSeg, kBase>(sc, g, stk, t_best, id_best, wc, perm, seg);
+    return traverse_loop<B, S, kAny, kCount, false, kPerm, kSeg, kBase, kUni>(sc, g, stk, t_best, id_best, wc, perm, seg);
 }
 
-template <int B, int S, bool kCount, bool kPerm = false, int kBase = 0>
+template <int B, int S, bool kCount, bool kPerm = false, int kBase = 0, bool kUni = true>
 __device__ __forceinline__ int closest_hit(const TraceView& sc, const RayPre& r, int* stk, float& t_best,
                                            int& id_best, WorkCount& wc) {
-    return traverse<B, S, false, kCount, kPerm, false, kBase>(sc, r, stk, t_best, id_best, wc);
+    return traverse<B, S, false, kCount, kPerm, false, kBase, kUni>(sc, r, stk, t_best, id_best, wc);
 }
 
-template <int B, int S, bool kCount, bool kPerm = false>
+template <int B, int S, bool kCount, bool kPerm = false, bool kUni = true>
 __device__ __forceinline__ bool any_hit(const TraceView& sc, const RayPre& r, int* stk, WorkCount& wc) {
     float t;
     int id;
-    return traverse<B, S, true, kCount, kPerm>(sc, r, stk, t, id, wc) >= 0;
+    return traverse<B, S, true, kCount, kPerm, false, 0, kUni>(sc, r, stk, t, id, wc) >= 0;
 }
 
 // 32-bit hash of Jarzynski and Olano, "Hash Functions for GPU Rendering",
@@ -725,7 +732,7 @@ __device__ float4 shade_lambert(const TraceView& v, RayPre& r, int64_t& out, int
         keep[at + B] = __float_as_int(r.dy);
         keep[at + 2 * B] = __float_as_int(r.dz);
         keep[at + 3 * B] = (int)(uint32_t)out;
-        slot = closest_hit<B, S, kCount, kPerm, 4>(sc, r, stk, t, id, wc);
+        slot = closest_hit<B, S, kCount, kPerm, 4, false>(sc, r, stk, t, id, wc);
         uint32_t lane;   // (formed here, not kept from above)
         __asm__ volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
         r.dx = __int_as_float(keep[lane]);
@@ -759,7 +766,7 @@ __device__ float4 shade_lambert(const TraceView& v, RayPre& r, int64_t& out, int
         RayPre s;
         light_ray(v, os, s);
         ++n_shadow;
-        if (any_hit<B, S, kCount, kPerm>(sc, s, stk, wc)) vis = 0.0f;
+        if (any_hit<B, S, kCount, kPerm, !kSolo>(sc, s, stk, wc)) vis = 0.0f;
     }
     const float lam = ndl > 0.0f ? ndl : 0.0f;
     const float3 a = albedo_of(id);
