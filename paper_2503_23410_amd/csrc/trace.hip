@@ -978,7 +978,7 @@ __device__ __forceinline__ void trace_item(const TraceView& v, int64_t k, int* s
 // 2560x1440 full-resolution view on the 1.13M terrain takes 0.50 ms instead
 // of 0.45 and LMFR(1.8) at 8K 1.36 ms instead of 1.25.
 #define kTraceWaves(lambert) __attribute__((amdgpu_waves_per_eu((lambert) ? 8 : 5)))
-#define kFiveWaves kTraceWaves(false)
+#define kListWaves(lambert) __attribute__((amdgpu_waves_per_eu((lambert) ? 6 : 5)))
 #define kBatchWaves(lambert, phased) __attribute__((amdgpu_waves_per_eu((phased) || (lambert) ? 8 : 5)))
 
 // Workgroups are dispatched to the 8 XCDs round-robin (workgroup id b runs
@@ -1047,18 +1047,33 @@ __global__ __launch_bounds__(kQueueBlock) kBatchWaves(false, true) void k_trace_
     path_bounce<kQueueBlock, S>(v, r, p, __float_as_int(e0.w), bounce, stack, true);
 }
 
-// List mode: items item_list[0 .. *item_count), by a fixed grid that takes as
-// many rounds as the list needs.  The listed rays are the longest of a frame
-// (they skim the surface), and a short list leaves most of the chip idle while
-// the last of them walk their nodes one after the other: up to kSplitItems
-// Lambert-shaded items (those that fill the chip once) are therefore followed
-// by kSplit lanes each, a part of the way per lane.  71 thousand listed rays
-// of a right eye on the 4.52M terrain took 0.216 ms with a lane each, 0.175
-// with four; whole frames with 1 / 4 / 8 / 16 / 32 lanes: 554 / 527 / 534 /
-// 646 / 733 us (centred gaze), 542 / 503 / 502 / 582 / 654 us (off centre).
+// List mode: items item_list[0 .. *item_count), by a grid for the longest list
+// (workgroups past the count exit at once).  A fixed grid of 8192 workgroups
+// that took long lists in rounds left the last round to a few of them: all
+// 1.06M texels of an eye on the 1.13M terrain 442 -> 342 us, path-traced 1328
+// -> 1046 us.  Lambert and path shading have kernels of their own: in one
+// kernel the two forms below and the path code spilled 88 registers (binocular
+// frame with 92 thousand holes 521 -> 495 us).
+//
+// The texels that a left eye leaves uncovered are mostly the longest rays of
+// a frame (they skim the surface), and a short list of them leaves most of
+// the chip idle while the last of them walk their nodes one after the other:
+// up to kSplitItems Lambert-shaded items, when they are at most one in
+// kSplitShare of the view's, are therefore followed by kSplit lanes each, a
+// part of the way per lane.  A longer list fills the chip with a lane each,
+// and one that holds a larger share of the texels holds ordinary rays as
+// well, which are too short to share.  Whole frames, one lane -> four: 1.06M
+// texels on the 4.52M terrain, 28 thousand listed 523 -> 475 us, 86 thousand
+// 535 -> 489, 145 thousand 563 -> 557, 188 thousand 900 -> 903, 346 thousand
+// 949 -> 1036; 4.25M texels, 100 thousand 1205 -> 1137, 227 thousand 1206 ->
+// 1188, 330 thousand 1232 -> 1250; 487 thousand texels on the 1.13M terrain, 66
+// thousand 255 -> 251, 106 thousand 265 -> 279; 76 thousand texels, 66
+// thousand listed 122 -> 124.  Eight lanes and more were slower (four / 8 / 16 /
+// 32: 527 / 534 / 646 / 733 us).
 constexpr int kSplit = 4;
-constexpr int kListBlocks = 8192;
-constexpr int kSplitItems = 98304;
+constexpr int kSplitItems = 196608;
+constexpr int kSplitShare = 5;
+static_assert(kSplit <= kSplitShare, "one lane per item of the view is lanes enough");
 
 // Segment c of the kSplit equal ones that cut the ray's way through the scene's
 // box; the first reaches back to the origin and the last on to infinity, and
@@ -1087,7 +1102,7 @@ __device__ void trace_item_split(const TraceView& v, int64_t k, int c, int* stk)
     WorkCount wc;
     float t;
     int id;
-    int slot = traverse<B, S, false, false, false, true>(v, r, stk, t, id, wc, ray_segment(v, r, c));
+    int slot = traverse<B, S, false, false, false, true, 0, false>(v, r, stk, t, id, wc, ray_segment(v, r, c));
     // the group's least (t, id); lanes without a hit hold (+inf, -1)
     auto least = [&](float ot, int oi, int os) {
         if (ot < t || (ot == t && oi < id)) {
@@ -1116,7 +1131,7 @@ __device__ void trace_item_split(const TraceView& v, int64_t k, int c, int* stk)
             light_ray(v, os, s);
             float ts;
             int ids;
-            int any = traverse<B, S, true, false, true, true>(v, s, stk, ts, ids, wc, ray_segment(v, s, c)) >= 0;
+            int any = traverse<B, S, true, false, true, true, 0, false>(v, s, stk, ts, ids, wc, ray_segment(v, s, c)) >= 0;
 #pragma unroll
             for (int m = 1; m < kSplit; m <<= 1) any |= __shfl_xor(any, m, 64);
             if (any) vis = 0.0f;
@@ -1133,16 +1148,17 @@ __device__ void trace_item_split(const TraceView& v, int64_t k, int c, int* stk)
     if (v.out_p) v.out_p[out] = p;
 }
 
-template <int B, int S>
-__global__ __launch_bounds__(B) kFiveWaves void k_trace_list(const TraceView v) {
+// kLambert: the view is Lambert-shaded (69 VGPRs, seven waves per SIMD; a
+// budget of eight spilled 14 registers, 494 -> 511 us), else path-traced.
+template <int B, int S, bool kLambert>
+__global__ __launch_bounds__(B) kListWaves(kLambert) void k_trace_list(const TraceView v) {
     __shared__ int stack[lds_entries(S) * B];
-    const int count = *v.item_count;
-    if (v.shade_mode != VAFR_SHADE_PATH && count <= kSplitItems) {
-        for (int64_t q = (int64_t)blockIdx.x * B + threadIdx.x; q < kSplit * (int64_t)count; q += (int64_t)gridDim.x * B)
-            trace_item_split<B, S>(v, v.item_list[q / kSplit], (int)(q % kSplit), stack);
-    } else {
-        for (int64_t q = (int64_t)blockIdx.x * B + threadIdx.x; q < count; q += (int64_t)gridDim.x * B)
-            trace_item<B, S, false>(v, v.item_list[q], stack, nullptr);
+    const int64_t count = *v.item_count;
+    const int64_t q = (int64_t)blockIdx.x * B + threadIdx.x;
+    if (kLambert && count <= kSplitItems && kSplitShare * count <= v.n_items) {
+        if (q < kSplit * count) trace_item_split<B, S>(v, v.item_list[q / kSplit], (int)(q % kSplit), stack);
+    } else if (q < count) {
+        trace_item<B, S, false, false, kLambert, kLambert>(v, v.item_list[q], stack, nullptr);
     }
 }
 
@@ -1231,10 +1247,12 @@ __global__ __launch_bounds__(kPlanThreads) void k_trace_plan(uint32_t* __restric
 template <int S>
 void launch_single(const TraceView& v, int64_t blocks, hipStream_t stream, unsigned long long* counters) {
     constexpr int B = kTraceBlockSingle;
-    if (v.item_list)
-        hipLaunchKernelGGL((k_trace_list<B, S>), dim3((unsigned)std::min<int64_t>(kSplit * blocks, kListBlocks)), dim3(B), 0,
-                           stream, v);
-    else if (counters)
+    if (v.item_list) {
+        if (v.shade_mode == VAFR_SHADE_PATH)
+            hipLaunchKernelGGL((k_trace_list<B, S, false>), dim3((unsigned)blocks), dim3(B), 0, stream, v);
+        else
+            hipLaunchKernelGGL((k_trace_list<B, S, true>), dim3((unsigned)blocks), dim3(B), 0, stream, v);
+    } else if (counters)
         hipLaunchKernelGGL((k_trace<B, S, true, false>), dim3((unsigned)blocks), dim3(B), 0, stream, v, counters);
     else if (v.shade_mode == VAFR_SHADE_PATH)
         hipLaunchKernelGGL((k_trace<B, S, false, false>), dim3((unsigned)blocks), dim3(B), 0, stream, v, counters);
