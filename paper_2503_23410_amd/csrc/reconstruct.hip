@@ -266,8 +266,19 @@ __device__ __forceinline__ void sample_vafr(const ReconView& v, const Stage& st,
 //    FP32 would lose the small q's digits).
 __device__ __forceinline__ float lafr_u(const ReconView& v, float z, double r2) {
     if (z <= v.lf_zef) return powf(z * v.lf_fa1, v.lf_inv_fa);
+    // (branches, not both logarithms and a select: one row per thread in a
+    // batch, 3840x2160, LaFR 73 -> 42 us, LMFR 51 -> 42 us)
     const double q = r2 * v.lf_inv_r2;
-    const float lq = q > 0.5 ? log1pf((float)(q - 1.0)) : logf((float)q);
+    float lq;
+    if (q > 0.5) {
+        float qm = (float)fma(r2, v.lf_inv_r2, -1.0);
+        __asm__ volatile("" : "+v"(qm));
+        lq = log1pf(qm);
+    } else {
+        float ql = (float)q;
+        __asm__ volatile("" : "+v"(ql));
+        lq = logf(ql);
+    }
     const float omz = fmaxf(-lq * v.lf_half_inv_lnl, 0.0f);
     const float eps = fminf(omz / ((1.0f - omz) * v.lf_k), 1.0f);
     const float s = fmaf(-4.0f * (float)M_1_PI, asinf(__builtin_amdgcn_sqrtf(0.5f * eps)), 1.0f);
