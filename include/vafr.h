@@ -367,10 +367,12 @@ typedef struct {
 } vafr_view;
 
 /* Launch shape of a batch: traversal workgroup size (64, 128 or 256 rays),
- * display rows each reconstruction thread writes (1, 2, 4 or 8; a
- * workgroup of 256 threads covers 64 x 4 recon_rows pixels; VaFR views of
- * large displays that share no workgroups with another eye take twice the
- * rows, up to 8, and two eyes of smaller displays half of 4 or 8) and whether frames are replayed from a hipGraph. */
+ * display rows each reconstruction thread writes and whether frames are
+ * replayed from a hipGraph.  recon_rows 1, 2 and 8 hold for every view (a
+ * workgroup of 256 threads covers 64 x 4 recon_rows pixels); 4, the default,
+ * gives each view the rows that measured fastest: 2 to two eyes that share
+ * workgroups, 8 to other VaFR views of 14,000,000 pixels or more, 4 to the
+ * rest. */
 typedef struct {
     int32_t trace_block;
     int32_t recon_rows;
@@ -401,8 +403,8 @@ int vafr_batch_create(int32_t max_views, const vafr_batch_config* cfg, vafr_batc
  * only when all 4 descriptor slots are still in flight. */
 int vafr_batch_run(vafr_batch batch, const vafr_view* views, int32_t n_views, hipStream_t stream);
 
-/* Times every traversal workgroup size and reconstruction tile height on
- * these views (reps frames each, on `stream`) and keeps the fastest in the
+/* Times every traversal workgroup size and every different reconstruction
+ * launch on these views (reps frames each, on `stream`) and keeps the fastest in the
  * batch's configuration; the choice is also returned in *chosen (nullable). */
 int vafr_batch_autotune(vafr_batch batch, const vafr_view* views, int32_t n_views, int32_t reps, hipStream_t stream,
                         vafr_batch_config* chosen);

@@ -86,6 +86,7 @@ struct vafr_batch_s {
     std::vector<int64_t> qoff;       // first path-state entry of each view
     int64_t queue_items = 0;         // path-state entries the frame needs
     int bounces = 0;                 // most bounces of a path-mode view of the frame
+    int recon_rows = 0;              // rows per thread of the frame's reconstruction, or kReconRowsMixed
     bool profiling = false;
     double stage_sum[3] = {0, 0, 0};   // accumulated stage times (ms)
     int64_t stage_frames = 0;
@@ -181,23 +182,23 @@ int describe(vafr_batch b, const vafr_view* views, int32_t n, int32_t* trace_blo
             if (int rc2 = make_recon_view(w.layout, w.gaze, w.lp_rgba_dev, w.img_rgba_dev, &r)) return rc2;
             if (!b->rv.empty() && pairable(b->rv.back(), r)) {
                 ReconView& first = b->rv.back();
-                rsum -= recon_blocks_of(first, b->cfg.recon_rows);
+                rsum -= recon_blocks_of(first, first.rows);
                 first.lp2 = r.lp;
                 first.img2 = r.img;
-                first.rows_shift = b->cfg.recon_rows >= 4 && (int64_t)r.width * r.height < kTallPixels ? -1 : 0;
-                rsum += recon_blocks_of(first, b->cfg.recon_rows);
+                first.rows = recon_rows_of(first, b->cfg.recon_rows);
+                rsum += recon_blocks_of(first, first.rows);
                 if (rsum > 0x7fffffff) return fail(VAFR_E_UNSUPPORTED, "too many pixels in one batch");
                 b->rb.back() = (int32_t)rsum;
                 continue;
             }
-            // (until it pairs)
-            r.rows_shift = r.mode == kModeVafr && b->cfg.recon_rows <= 4 && (int64_t)r.width * r.height >= kTallPixels;
-            rsum += recon_blocks_of(r, b->cfg.recon_rows);
+            r.rows = recon_rows_of(r, b->cfg.recon_rows);   // (until it pairs)
+            rsum += recon_blocks_of(r, r.rows);
             if (rsum > 0x7fffffff) return fail(VAFR_E_UNSUPPORTED, "too many pixels in one batch");
             b->rv.push_back(r);
             b->rb.push_back((int32_t)rsum);
         }
     }
+    b->recon_rows = recon_launch_rows(b->rv.data(), (int)b->rv.size(), b->cfg.recon_rows);
     *trace_blocks = (int32_t)tsum;
     *recon_blocks = (int32_t)rsum;
     *queue_blocks = (int32_t)qsum;
@@ -362,7 +363,7 @@ int graph_for(vafr_batch b, int32_t trace_blocks, int32_t recon_blocks, int32_t 
         if (g.n_trace == nt && g.n_recon == nr && g.trace_blocks == trace_blocks && g.recon_blocks == recon_blocks &&
             g.queue_blocks == queue_blocks && g.bounces == (queue_blocks > 0 ? b->bounces : 0) &&
             g.lambert == b->lambert && g.trace_block == b->cfg.trace_block &&
-            g.recon_rows == b->cfg.recon_rows && g.stack == b->stack && g.timed == b->profiling) {
+            g.recon_rows == b->recon_rows && g.stack == b->stack && g.timed == b->profiling) {
             *out = &g;
             return VAFR_OK;
         }
@@ -393,7 +394,7 @@ int graph_for(vafr_batch b, int32_t trace_blocks, int32_t recon_blocks, int32_t 
     g.bounces = queue_blocks > 0 ? b->bounces : 0;
     g.lambert = b->lambert;
     g.trace_block = b->cfg.trace_block;
-    g.recon_rows = b->cfg.recon_rows;
+    g.recon_rows = b->recon_rows;
     g.stack = b->stack;
     g.timed = b->profiling;
     VAFR_HIP(hipGraphCreate(&g.graph, 0));
@@ -554,7 +555,7 @@ int run_locked(vafr_batch b, const vafr_view* views, int32_t n, hipStream_t stre
         if (b->profiling) VAFR_HIP(hipEventRecord(s.ev[2], stream));
         if (int rc = launch_reconstruct_batch(reinterpret_cast<const ReconView*>(s.dev + b->off_rv),
                                               reinterpret_cast<const int32_t*>(s.dev + b->off_rb),
-                                              (int32_t)b->rv.size(), rblocks, b->cfg.recon_rows, stream))
+                                              (int32_t)b->rv.size(), rblocks, b->recon_rows, stream))
             return rc;
         if (b->profiling) VAFR_HIP(hipEventRecord(s.ev[3], stream));
     }
@@ -675,11 +676,14 @@ extern "C" int vafr_batch_autotune(vafr_batch b, const vafr_view* views, int32_t
         if (ms < best_ms) { best_ms = ms; best = c; }
     }
     if (!rc) {
+        // (4 rows stand for the same launch as 2 where every view is a pair)
+        const bool pairs = std::all_of(b->rv.begin(), b->rv.end(), [](const ReconView& r) { return r.lp2 != nullptr; });
+        if (pairs && best.recon_rows == 4) best.recon_rows = 2;
         const vafr_batch_config base = best;
         for (int rows : {1, 2, 4, 8}) {
             vafr_batch_config c = base;
             c.recon_rows = rows;
-            if (c.recon_rows == base.recon_rows) continue;
+            if (c.recon_rows == base.recon_rows || (pairs && rows == 4)) continue;
             float ms;
             if ((rc = time_cfg(c, &ms))) break;
             if (ms < best_ms) { best_ms = ms; best = c; }

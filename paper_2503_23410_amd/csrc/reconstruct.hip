@@ -578,20 +578,39 @@ __global__ __launch_bounds__(kReconThreads) void k_recon(const ReconView v) {
     recon_tile<P, M>(v, blockIdx.x, st);
 }
 
-// Batched launch over several views (block_end: running tile counts).
+// Batched launch over several views (block_end: running tile counts).  The
+// view of workgroup b, and b's number within it.
+__device__ __forceinline__ const ReconView& batch_view(const ReconView* __restrict__ views,
+                                                       const int32_t* __restrict__ block_end, int32_t n_views,
+                                                       int& b) {
+    int vid = 0;
+    while (vid + 1 < n_views && b >= block_end[vid]) ++vid;
+    b -= vid ? block_end[vid - 1] : 0;
+    return views[vid];
+}
+
+// Every view with P rows per thread (pairs take 1, 2 or 8, see recon_rows_of).
 template <int P>
 __global__ __launch_bounds__(kReconThreads) void k_recon_batch(const ReconView* __restrict__ views,
                                                              const int32_t* __restrict__ block_end, int32_t n_views) {
     __shared__ Stage st;
-    const int b = blockIdx.x;
-    int vid = 0;
-    while (vid + 1 < n_views && b >= block_end[vid]) ++vid;
-    const int first = vid ? block_end[vid - 1] : 0;
-    const ReconView& v = views[vid];
-    if (v.lp2 && P >= 4 && v.rows_shift < 0) recon_tile<(P + 1) / 2, kModeVafr, true>(v, b - first, st);
-    else if (v.lp2) recon_tile<P, kModeVafr, true>(v, b - first, st);
-    else if (P <= 4 && v.rows_shift > 0) recon_tile<2 * P, kModeVafr>(v, b - first, st);
-    else recon_tile<P, -1>(v, b - first, st);
+    int b = blockIdx.x;
+    const ReconView& v = batch_view(views, block_end, n_views, b);
+    if (P != 4 && v.lp2) recon_tile<P, kModeVafr, true>(v, b, st);
+    else recon_tile<P, -1>(v, b, st);
+}
+
+// Views of different rows: pairs with 2, single VaFR views of large displays
+// with 8, all others with 4.
+__global__ __launch_bounds__(kReconThreads) void k_recon_mixed(const ReconView* __restrict__ views,
+                                                               const int32_t* __restrict__ block_end,
+                                                               int32_t n_views) {
+    __shared__ Stage st;
+    int b = blockIdx.x;
+    const ReconView& v = batch_view(views, block_end, n_views, b);
+    if (v.lp2) recon_tile<2, kModeVafr, true>(v, b, st);
+    else if (v.rows == 8) recon_tile<8, kModeVafr>(v, b, st);
+    else recon_tile<4, -1>(v, b, st);
 }
 
 }  // namespace
@@ -599,7 +618,7 @@ __global__ __launch_bounds__(kReconThreads) void k_recon_batch(const ReconView* 
 bool recon_rows_ok(int rows) { return rows == 1 || rows == 2 || rows == 4 || rows == 8; }
 
 int64_t recon_blocks_of(const ReconView& v, int rows) {
-    const int tile_h = kWaves * (v.rows_shift < 0 ? rows / 2 : rows << v.rows_shift);
+    const int tile_h = kWaves * rows;
     return (int64_t)((v.width + kTileW - 1) / kTileW) * ((v.height + tile_h - 1) / tile_h);
 }
 
@@ -621,6 +640,7 @@ const void* recon_batch_kernel(int rows) {
         case 2: return reinterpret_cast<const void*>(&k_recon_batch<2>);
         case 4: return reinterpret_cast<const void*>(&k_recon_batch<4>);
         case 8: return reinterpret_cast<const void*>(&k_recon_batch<8>);
+        case kReconRowsMixed: return reinterpret_cast<const void*>(&k_recon_mixed);
         default: return nullptr;
     }
 }
@@ -628,9 +648,11 @@ const void* recon_batch_kernel(int rows) {
 int launch_reconstruct_batch(const ReconView* views_dev, const int32_t* block_end_dev, int32_t n_views,
                              int32_t blocks, int rows, hipStream_t stream) {
     if (blocks <= 0) return VAFR_OK;
-    if (!recon_rows_ok(rows)) return fail(VAFR_E_ARG, "reconstruction rows per thread must be 1, 2, 4 or 8");
+    if (rows != kReconRowsMixed && !recon_rows_ok(rows))
+        return fail(VAFR_E_ARG, "reconstruction rows per thread must be 1, 2, 4 or 8");
     const dim3 g((unsigned)blocks), t(kReconThreads);
     switch (rows) {
+        case kReconRowsMixed: hipLaunchKernelGGL(k_recon_mixed, g, t, 0, stream, views_dev, block_end_dev, n_views); break;
         case 1: hipLaunchKernelGGL(k_recon_batch<1>, g, t, 0, stream, views_dev, block_end_dev, n_views); break;
         case 2: hipLaunchKernelGGL(k_recon_batch<2>, g, t, 0, stream, views_dev, block_end_dev, n_views); break;
         case 4: hipLaunchKernelGGL(k_recon_batch<4>, g, t, 0, stream, views_dev, block_end_dev, n_views); break;

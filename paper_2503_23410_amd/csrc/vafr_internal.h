@@ -317,29 +317,43 @@ struct ReconView {
     // display (the other eye), reconstructed in the same pass; or null
     const float4* lp2;
     float4* img2;
-    // batched frames: an unpaired VaFR view of a large display takes tiles of
-    // twice the batch's rows per thread (1; rows <= 4), a pair of smaller
-    // displays half of them (-1; rows >= 4)
-    int32_t rows_shift;
+    int32_t rows;       // batched frames: rows per thread of the view's tiles (recon_rows_of)
 };
 
 // Reconstruction workgroups have kReconThreads threads (4 waves); `rows` is
 // the number of display rows each thread writes, so a tile is 64 x 4 rows.
 constexpr int kReconThreads = 256;
 bool recon_rows_ok(int rows);
-constexpr int kBatchReconRowsDefault = 4;   // batches: binocular pairs fit 64 VGPRs at 4 rows, not at 8
+constexpr int kBatchReconRowsDefault = 4;
 // VaFR displays from this many pixels on are mapped 8 rows per thread, smaller
 // ones 4 (one view, rows 2 / 4 / 8: 1281x721 9.8 / 10.3 / 11.8 us, 1921x1083
 // 16 / 14 / 20 us, 3840x2160 35 / 30 / 35 us, 5120x2880 59 / 47 / 47 us,
 // 7680x4320 125 / 100 / 89 us): a small display needs the workgroups, a large
 // one the fewer tile set-ups.
 constexpr int64_t kTallPixels = 14000000;
-// Binocular pairs in batches of 4 or 8 rows halve them below the same size (one
-// pair, rows 8 / 4 / 2: 640x360 26 / 17.5 / 13.9 us, 2560x1440 43 / 36 / 33 us,
-// 3840x2160 70 / 60 / 57 us, but 5120x2880 91 / 83 / 88 us and 7680x4320 185 /
-// 177 / 173 - 185 us from one card to the next).
 constexpr int kReconRowsDense = 2;          // LMFR / LaFR (8K: 141 us against 147 at 8 rows, 3839x2161: 34 against 43)
 int64_t recon_blocks_of(const ReconView& v, int rows);
+// Rows per thread that a batch configured for `rows` gives view v: 1, 2 and 8
+// are taken as they are; 4, the default, stands for the faster height by
+// pairing and display size.  Pairs do most per pixel and take 2 (one pair,
+// rows 8 / 4 / 2: 640x360 26 / 17 / 14 us, 2560x1440 42 / 39 / 32, 3840x2160
+// 68 / 55 / 54, 5120x2880 92 / 83 / 78, 7680x4320 182 / 176 / 160; at 4400x3000
+// 4 are faster, 90 / 81 / 86).
+inline int recon_rows_of(const ReconView& v, int rows) {
+    if (rows != 4 || v.mode != kModeVafr) return rows;
+    return v.lp2 ? 2 : (int64_t)v.width * v.height >= kTallPixels ? 8 : 4;
+}
+// Rows per thread of the kernel that maps a frame's n views (their `rows` set):
+// kReconRowsMixed unless all of them take 2 or all take 4.  A large display
+// alone (8 rows) goes there too: k_recon_batch<8> holds pairs of 8 rows as
+// well, which costs it two waves per SIMD (91 us at 8K against 87).
+constexpr int kReconRowsMixed = 0;
+inline int recon_launch_rows(const ReconView* v, int n, int rows) {
+    if (rows != 4 || n == 0) return rows;
+    for (int i = 1; i < n; ++i)
+        if (v[i].rows != v[0].rows) return kReconRowsMixed;
+    return v[0].rows == 8 ? kReconRowsMixed : v[0].rows;
+}
 // Rows per thread chosen by mapping and display size.
 int launch_reconstruct(const ReconView& v, hipStream_t stream);
 int launch_reconstruct_batch(const ReconView* views_dev, const int32_t* block_end_dev, int32_t n_views,

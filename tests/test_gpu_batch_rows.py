@@ -1,0 +1,62 @@
+"""The autotuner over reconstruction heights (GPU): it times each different
+launch once, so a frame of binocular pairs, where 4 rows stand for the launch
+of 2, is never reported as 4."""
+import pytest
+
+from paper_2503_23410_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("W,H", [(65, 33), (640, 360)])
+@pytest.mark.parametrize("eyes", [1, 2])
+def test_autotuned_rows_name_a_launch(W, H, eyes):
+    import torch
+    from paper_2503_23410_amd import vafr as V
+    scene, sh, L = V.Scene(*I.soup_scene(40, seed=2)), V.shading(), V.Layout.vafr(V.display(W, H))
+    lp = [torch.empty((L.n_texels, 4), device="cuda") for _ in range(eyes)]
+    img = [torch.full((W * H, 4), float("nan"), device="cuda") for _ in range(eyes)]
+    views = [V.view(V.VAFR_VIEW_VAFR, scene, V.camera(I.soup_camera()), V.gaze(0.6 * W, 0.4 * H), sh, layout=L,
+                    lp_rgba=lp[k], img_rgba=img[k]) for k in range(eyes)]
+    for start in (4, 2):
+        b = V.Batch(2, recon_rows=start)
+        cfg = b.autotune(views, reps=2)
+        assert cfg["recon_rows"] in ((1, 2, 4, 8) if eyes == 1 else (1, 2, 8)) and b.config() == cfg
+        b.run(views)
+        for k in range(eyes):
+            one = torch.empty_like(img[k])
+            V.vafr_reconstruct(L, V.gaze(0.6 * W, 0.4 * H), lp[k], one)
+            torch.cuda.synchronize()
+            assert torch.equal(one, img[k])
+        b.close()
+
+
+# one frame with every form: pairs, views alone on small and large displays
+# (either side of 14,000,000 pixels) and a dense view, in the default height
+@pytest.mark.parametrize("use_graph", [False, True])
+def test_mixed_heights_equal_the_per_view_calls(use_graph):
+    import torch
+    from paper_2503_23410_amd import vafr as V
+    scene, sh = V.Scene(*I.soup_scene(40, seed=2)), V.shading()
+    cam = V.camera(I.soup_camera())
+    sizes = [(130, 65), (130, 65), (3742, 3742), (3741, 3742), (200, 101)]
+    gaze = [(40.0, 30.0), (40.0, 30.0), (100.0, 3000.0), (1800.5, 1900.0), (90.0, 20.0)]
+    kind = [V.VAFR_VIEW_VAFR] * 4 + [V.VAFR_VIEW_LMFR]
+    L = {s: (V.Layout.lmfr if s == (200, 101) else V.Layout.vafr)(V.display(*s), *([2.0] if s == (200, 101) else []))
+         for s in set(sizes)}
+    lp = [torch.empty((L[s].n_texels, 4), device="cuda") for s in sizes]
+    img = [torch.full((s[0] * s[1], 4), float("nan"), device="cuda") for s in sizes]
+    views = [V.view(kd, scene, cam, V.gaze(*g), sh, layout=L[s], lp_rgba=p, img_rgba=i)
+             for kd, s, g, p, i in zip(kind, sizes, gaze, lp, img)]
+    b = V.Batch(5, use_graph=use_graph)
+    for chosen in (range(5), range(2), [2], [3, 4], [0, 1, 4]):    # every kernel that the default height takes
+        for i in img:
+            i.fill_(float("nan"))
+        b.run([views[k] for k in chosen])
+        for k in chosen:
+            one = torch.empty_like(img[k])
+            (V.lmfr_reconstruct if kind[k] == V.VAFR_VIEW_LMFR else V.vafr_reconstruct)(L[sizes[k]], V.gaze(*gaze[k]),
+                                                                                        lp[k], one)
+            torch.cuda.synchronize()
+            assert torch.equal(one, img[k]), (list(chosen), k)
+    b.close()
