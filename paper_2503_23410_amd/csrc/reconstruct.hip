@@ -623,11 +623,13 @@ int64_t recon_blocks_of(const ReconView& v, int rows) {
 }
 
 int launch_reconstruct(const ReconView& v, hipStream_t stream) {
-    const int rows = v.mode != kModeVafr ? kReconRowsDense : (int64_t)v.width * v.height < kTallPixels ? 4 : 8;
+    const int64_t pixels = (int64_t)v.width * v.height;
+    const int rows = v.mode != kModeVafr ? kReconRowsDense : pixels < kShortPixels ? 2 : pixels < kTallPixels ? 4 : 8;
     const int64_t blocks = recon_blocks_of(v, rows);
     if (blocks > 0x7fffffff) return fail(VAFR_E_UNSUPPORTED, "display too large");
     const dim3 g((unsigned)blocks), t(kReconThreads);
     if (v.mode != kModeVafr) hipLaunchKernelGGL((k_recon<kReconRowsDense, kModeLmfr>), g, t, 0, stream, v);
+    else if (rows == 2) hipLaunchKernelGGL((k_recon<2, kModeVafr>), g, t, 0, stream, v);
     else if (rows == 4) hipLaunchKernelGGL((k_recon<4, kModeVafr>), g, t, 0, stream, v);
     else hipLaunchKernelGGL((k_recon<8, kModeVafr>), g, t, 0, stream, v);
     VAFR_HIP(hipGetLastError());

@@ -325,11 +325,17 @@ struct ReconView {
 constexpr int kReconThreads = 256;
 bool recon_rows_ok(int rows);
 constexpr int kBatchReconRowsDefault = 4;
-// VaFR displays from this many pixels on are mapped 8 rows per thread, smaller
-// ones 4 (one view, rows 2 / 4 / 8: 1281x721 9.8 / 10.3 / 11.8 us, 1921x1083
-// 16 / 14 / 20 us, 3840x2160 35 / 30 / 35 us, 5120x2880 59 / 47 / 47 us,
-// 7680x4320 125 / 100 / 89 us): a small display needs the workgroups, a large
-// one the fewer tile set-ups.
+// Per-view calls map VaFR displays of fewer pixels than kShortPixels 2 rows per
+// thread, those from kTallPixels on 8, the others 4: a small display needs the
+// workgroups, a large one the fewer tile set-ups.  One view, rows 1 / 2 / 4 / 8,
+// gaze in the middle: 960x540 9.1 / 8.1 / 7.9 / 12.1 us (calls below this size
+// take the 7.3 us that it takes to issue one), 1280x720 10.3 / 9.4 / 11.0 /
+// 12.9, 1281x721 12.6 / 10.1 / 11.5 / 13.3, 1600x900 15.2 / 12.0 / 12.6 / 16.6 and
+// off centre 12.8 / 10.5 / 9.0 / 11.5, 1921x1083 20 / 16 / 14 / 20, 3840x2160
+// 51 / 38 / 33 / 33, 3840x3840 86 / 62 / 53 / 48; 5120x2880 2 / 4 / 8: 59 / 47 /
+// 47, 7680x4320 125 / 100 / 89.  (Batches keep 4 for small displays too: their
+// views fill the chip together.)
+constexpr int64_t kShortPixels = 1200000;
 constexpr int64_t kTallPixels = 14000000;
 constexpr int kReconRowsDense = 2;          // LMFR / LaFR (8K: 141 us against 147 at 8 rows, 3839x2161: 34 against 43)
 int64_t recon_blocks_of(const ReconView& v, int rows);

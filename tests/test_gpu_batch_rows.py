@@ -1,6 +1,8 @@
-"""The autotuner over reconstruction heights (GPU): it times each different
-launch once, so a frame of binocular pairs, where 4 rows stand for the launch
-of 2, is never reported as 4."""
+"""Reconstruction heights (GPU).  The autotuner times each different launch
+once, so a frame of binocular pairs, where 4 rows stand for the launch of 2, is
+never reported as 4; and the display size where per-view calls change from 2
+to 4 rows."""
+import numpy as np
 import pytest
 
 from paper_2503_23410_amd import inputs as I
@@ -60,3 +62,24 @@ def test_mixed_heights_equal_the_per_view_calls(use_graph):
             torch.cuda.synchronize()
             assert torch.equal(one, img[k]), (list(chosen), k)
     b.close()
+
+
+# 1,199,000 and 1,200,000 pixels; the last tile row is 3 and 8 pixels high
+@pytest.mark.parametrize("W,H", [(1090, 1100), (1000, 1199), (1000, 1200)])
+@pytest.mark.parametrize("gaze", [(0.5, 0.5), (-0.1, 0.7)])
+def test_inverse_map_where_the_rows_change(O, W, H, gaze):
+    import torch
+    from paper_2503_23410_amd import vafr as V
+    g = (gaze[0] * W, gaze[1] * H)
+    L, ol = V.Layout.vafr(V.display(W, H)), O.Layout()
+    lp = I.random_lp(L.n_texels, seed=W + H)
+    img = torch.full((W * H, 4), float("nan"), device="cuda")
+    V.vafr_reconstruct(L, V.gaze(*g), torch.from_numpy(lp).cuda(), img)
+    torch.cuda.synchronize()
+    pix = np.unique(np.concatenate([np.random.default_rng(1).integers(0, W * H, 40000), (H - 1) * W + np.arange(W),
+                                    W * np.arange(H) + W - 1]))
+    p = O.film_pitch(W, H, *I.FOV)
+    ref = O.vafr_reconstruct(ol, lp, W, H, p, O.gaze_film(W, H, p, *g), pix)[0]
+    off = np.hypot(pix % W + 0.5 - g[0], pix // W + 0.5 - g[1])   # (no angle at the gaze point itself)
+    assert np.abs(img.cpu().numpy()[pix] - ref)[off > 1e-3].max() <= 2e-3
+    assert not torch.isnan(img).any()
