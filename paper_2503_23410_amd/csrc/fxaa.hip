@@ -26,6 +26,14 @@
 // is the search: a wave walks on until the last of its 64 searches has ended.
 // Windows of 2 to 16 columns on either side and 4 to 10 rows, and tiles of 8,
 // 12 or 16 columns, measured 34-44 us.
+//
+// A layout of fewer than kFxaaDirect texels does not fill the chip, and what
+// counts is how long one workgroup takes: it is faster without the window, one
+// thread per texel (14,164 texels: soup 9.8 -> 8.5 us, 1.13M terrain 11.5 -> 11.2,
+// noise 10.8 -> 11.6; 75,833: 11.6 -> 9.7, 11.5 -> 12.0, 10.7 -> 11.8; 282,968: 13.2
+// -> 12.2, 12.9 -> 13.1, 15.4 -> 19.6; 1,063,314: 21.9 -> 26.9, 32.3 -> 41.7).
+#include <type_traits>
+
 #include "vafr_internal.h"
 
 namespace vafr {
@@ -43,8 +51,10 @@ constexpr int kWindowTexels = (kFxaaCols + 2) * (kFxaaRows + 2 * kHalo);
 
 struct FxaaView {
     const int2* col;     // (rows, first texel) per column
-    const int4* tile;    // (first column, sector, sectors, 0) per workgroup
+    const int4* tile;    // staged form: (first column, sector, sectors, narrow) per workgroup
+    const int32_t* blk_col;   // direct form: column of the first texel of each workgroup
     int32_t n_cols;
+    int64_t n_texels;
     const float4* in;
     float4* out;
 };
@@ -78,11 +88,12 @@ __device__ __forceinline__ float4 texel_of(const FxaaView& v, const WinCol& w, i
     return v.in[(int64_t)w.off + r];
 }
 
-// Rows j and j + 1 of a column.
+// Rows j and j + 1 of a column (kStaged: from the window where they are there).
+template <bool kStaged>
 __device__ __forceinline__ void texel_pair(const FxaaView& v, const Window& win, const WinCol& w, int j, float4& a,
                                            float4& b) {
     const int rel = j - w.lo;
-    if ((unsigned)rel < (unsigned)w.pairs) {
+    if (kStaged && (unsigned)rel < (unsigned)w.pairs) {
         a = win.tex[w.base + rel];
         b = win.tex[w.base + rel + 1];
     } else {
@@ -92,12 +103,13 @@ __device__ __forceinline__ void texel_pair(const FxaaView& v, const Window& win,
 }
 
 // The column at angle t turns, linear between rows.
+template <bool kStaged>
 __device__ __forceinline__ float4 column_of(const FxaaView& v, const Window& win, const WinCol& cn, float t) {
     const float s = t * (float)cn.n - 0.5f;
     const float fs = floorf(s);
     const float w = s - fs;
     float4 a, b;
-    texel_pair(v, win, cn, (int)fs, a, b);
+    texel_pair<kStaged>(v, win, cn, (int)fs, a, b);
     return make_float4(a.x + w * (b.x - a.x), a.y + w * (b.y - a.y), a.z + w * (b.z - a.z), a.w + w * (b.w - a.w));
 }
 
@@ -107,28 +119,36 @@ __device__ __forceinline__ float luma(float4 p) { return (0.299f * p.x + 0.587f 
 __device__ __forceinline__ float curvature(float a, float m, float b) { return fabsf((a - m) + (b - m)); }
 
 // Texel (i, j); first: the column of window entry 0.
-__device__ float4 fxaa_texel(const FxaaView& v, const Window& win, int first, int i, int j) {
-    auto window = [&](int c) -> const WinCol& {
+template <bool kStaged>
+__device__ __forceinline__ float4 fxaa_texel(const FxaaView& v, const Window& win, int first, int i, int j) {
+    auto window = [&](int c) -> std::conditional_t<kStaged, const WinCol&, WinCol> {
         c = c < 0 ? 0 : (c >= v.n_cols ? v.n_cols - 1 : c);
-        return win.col[c - first];
+        if constexpr (kStaged) {
+            return win.col[c - first];
+        } else {
+            const int2 cc = v.col[c];
+            return WinCol{cc.x, cc.y, 0, 0, 0};
+        }
     };
     // records of the texel's column and of its outer and inner neighbours
-    const WinCol ci = uniform(window(i)), co = uniform(window(i + 1)), cn = uniform(window(i - 1));
+    const WinCol ci = kStaged ? uniform(window(i)) : window(i), co = kStaged ? uniform(window(i + 1)) : window(i + 1);
+    const WinCol cn = kStaged ? uniform(window(i - 1)) : window(i - 1);
     const int n = ci.n;
     const float t = ((float)j + 0.5f) / (float)n;
     const float dt = 1.0f / (float)n;
     // (rows j - 1 .. j + 1 of a texel's own column are staged)
-    const float4* own = win.tex + ci.base + (j - ci.lo);
-    const float4 M = own[0];
+    const float4* own = win.tex + (kStaged ? ci.base + (j - ci.lo) : 0);
+    const float4 M = kStaged ? own[0] : texel_of(v, ci, j);
     const float lM = luma(M);
-    const float lU = luma(own[1]), lD = luma(own[-1]);
-    const float lO = luma(column_of(v, win, co, t)), lI = luma(column_of(v, win, cn, t));
+    const float lU = luma(kStaged ? own[1] : texel_of(v, ci, j + 1));
+    const float lD = luma(kStaged ? own[-1] : texel_of(v, ci, j - 1));
+    const float lO = luma(column_of<kStaged>(v, win, co, t)), lI = luma(column_of<kStaged>(v, win, cn, t));
     const float lmax = fmaxf(fmaxf(fmaxf(lM, lU), fmaxf(lD, lO)), lI);
     const float lmin = fminf(fminf(fminf(lM, lU), fminf(lD, lO)), lI);
     const float range = lmax - lmin;
     if (range < fmaxf(kEdgeMin, lmax * kEdgeRel)) return M;
-    const float lOU = luma(column_of(v, win, co, t + dt)), lOD = luma(column_of(v, win, co, t - dt));
-    const float lIU = luma(column_of(v, win, cn, t + dt)), lID = luma(column_of(v, win, cn, t - dt));
+    const float lOU = luma(column_of<kStaged>(v, win, co, t + dt)), lOD = luma(column_of<kStaged>(v, win, co, t - dt));
+    const float lIU = luma(column_of<kStaged>(v, win, cn, t + dt)), lID = luma(column_of<kStaged>(v, win, cn, t - dt));
     // luma curvature across the radius (three angles) and across the angle
     // (three radii), centre line weighted twice
     const float across_r = (curvature(lID, lD, lOD) + 2.0f * curvature(lI, lM, lO)) + curvature(lIU, lU, lOU);
@@ -157,8 +177,8 @@ __device__ float4 fxaa_texel(const FxaaView& v, const Window& win, int first, in
             const float p = sgn * kStepAt[k];
             const float tt = t + p * dt;
             const int c = (int)p;
-            const float la = luma(column_of(v, win, window(radial ? i : i + c), radial ? tt : t));
-            const float lb = luma(column_of(v, win, window(radial ? across : i + c), radial ? tt : t_side));
+            const float la = luma(column_of<kStaged>(v, win, window(radial ? i : i + c), radial ? tt : t));
+            const float lb = luma(column_of<kStaged>(v, win, window(radial ? across : i + c), radial ? tt : t_side));
             const float l = 0.5f * (la + lb);
             if (fabsf(l - lLine) >= gScaled) {
                 dist[dir] = kStepAt[k];
@@ -174,14 +194,18 @@ __device__ float4 fxaa_texel(const FxaaView& v, const Window& win, int first, in
     const float s1 = fminf(fmaxf(fabsf(lAvg - lM) / range, 0.0f), 1.0f);
     const float s2 = (-2.0f * s1 + 3.0f) * (s1 * s1);
     const float off = fmaxf(edge, (s2 * s2) * kSubpix);
-    const float4 S = radial ? column_of(v, win, side > 0 ? co : cn, t) : own[side];
+    const float4 S = radial ? column_of<kStaged>(v, win, side > 0 ? co : cn, t)
+                            : kStaged ? own[side] : texel_of(v, ci, j + side);
     return make_float4(M.x + off * (S.x - M.x), M.y + off * (S.y - M.y), M.z + off * (S.z - M.z),
                        M.w + off * (S.w - M.w));
 }
 
 // First row of sector k of K in a column of n rows: the least j with
 // (j + 1/2) / n >= k / K.
+// (kNarrow: 2 n K + K fits 32 bits.)
+template <bool kNarrow>
 __device__ __forceinline__ int sector_row(int n, int k, int K) {
+    if (kNarrow) return (int)((2u * (uint32_t)n * (uint32_t)k + (uint32_t)K - 1u) / (2u * (uint32_t)K));
     return (int)((2 * (int64_t)n * k + K - 1) / (2 * K));
 }
 
@@ -198,7 +222,14 @@ __global__ __launch_bounds__(kFxaaThreads) void k_fxaa(const FxaaView v) {
         if (lane < last - first) {
             const int c = first + lane;
             const int2 cn = v.col[c];
-            const int r0 = sector_row(cn.x, k, K), r1 = sector_row(cn.x, k + 1, K);
+            int r0, r1;
+            if (tile.w) {
+                r0 = sector_row<true>(cn.x, k, K);
+                r1 = sector_row<true>(cn.x, k + 1, K);
+            } else {
+                r0 = sector_row<false>(cn.x, k, K);
+                r1 = sector_row<false>(cn.x, k + 1, K);
+            }
             w.n = cn.x;
             w.off = cn.y;
             w.lo = r0 - kHalo;
@@ -247,16 +278,34 @@ __global__ __launch_bounds__(kFxaaThreads) void k_fxaa(const FxaaView v) {
     for (int i = i0 + wave; i < i1; i += kWaves) {
         const WinCol w = uniform(win.col[i - first]);
         const int r0 = w.lo + kHalo, rows = w.pairs + 1 - 2 * kHalo;
-        if (lane < rows) v.out[(int64_t)w.off + r0 + lane] = fxaa_texel(v, win, first, i, r0 + lane);
+        if (lane < rows) v.out[(int64_t)w.off + r0 + lane] = fxaa_texel<true>(v, win, first, i, r0 + lane);
     }
+}
+
+// The direct form: one thread per texel, everything from the LP buffer.  The
+// column of texel k: from the workgroup's first column, walk forward (a
+// workgroup spans several columns only near the centre of the grid).
+__global__ __launch_bounds__(kTexelBlock) void k_fxaa_direct(const FxaaView v) {
+    const int64_t k = (int64_t)blockIdx.x * kTexelBlock + threadIdx.x;
+    if (k >= v.n_texels) return;
+    int c = v.blk_col[blockIdx.x];
+    while (c + 1 < v.n_cols && (int64_t)v.col[c + 1].y <= k) ++c;
+    __shared__ Window win;   // only named: the direct form does not read it, and no LDS is taken
+    v.out[k] = fxaa_texel<false>(v, win, 0, c, (int)(k - v.col[c].y));
 }
 
 }  // namespace
 
-int launch_fxaa(const LayoutDev& ld, int32_t n_cols, const float* in, float* out, hipStream_t stream) {
-    if (ld.n_fxaa_tiles <= 0) return VAFR_OK;
-    FxaaView v{ld.col, ld.fxaa_tile, n_cols, reinterpret_cast<const float4*>(in), reinterpret_cast<float4*>(out)};
-    hipLaunchKernelGGL(k_fxaa, dim3((unsigned)ld.n_fxaa_tiles), dim3(kFxaaThreads), 0, stream, v);
+int launch_fxaa(const LayoutDev& ld, int32_t n_cols, int64_t n_texels, const float* in, float* out,
+                hipStream_t stream) {
+    if (n_texels <= 0) return VAFR_OK;
+    FxaaView v{ld.col, ld.fxaa_tile, ld.blk_col, n_cols, n_texels, reinterpret_cast<const float4*>(in),
+               reinterpret_cast<float4*>(out)};
+    if (n_texels < kFxaaDirect)
+        hipLaunchKernelGGL(k_fxaa_direct, dim3((unsigned)((n_texels + kTexelBlock - 1) / kTexelBlock)),
+                           dim3(kTexelBlock), 0, stream, v);
+    else
+        hipLaunchKernelGGL(k_fxaa, dim3((unsigned)ld.n_fxaa_tiles), dim3(kFxaaThreads), 0, stream, v);
     VAFR_HIP(hipGetLastError());
     return VAFR_OK;
 }

@@ -174,7 +174,11 @@ int layout_device(vafr_layout L, const LayoutDev** out) {
             int32_t n = 1;
             for (int32_t c = i; c < std::min(i + kFxaaCols, L->n_cols); ++c) n = std::max(n, L->n_rows[c]);
             const int32_t sectors = (n + kFxaaRows - 1) / kFxaaRows;
-            for (int32_t k = 0; k < sectors; ++k) tile.push_back(make_int4(i, k, sectors, 0));
+            // the tile's window reaches one column further on either side
+            for (int32_t c : {i - 1, i + kFxaaCols})
+                if (c >= 0 && c < L->n_cols) n = std::max(n, L->n_rows[c]);
+            const int32_t narrow = (2 * (int64_t)n + 1) * sectors < (int64_t)1 << 32;
+            for (int32_t k = 0; k < sectors; ++k) tile.push_back(make_int4(i, k, sectors, narrow));
         }
         d.n_fxaa_tiles = (int32_t)tile.size();
         // one allocation; the small tables go up in one copy

@@ -47,7 +47,7 @@ struct LayoutDev {
     float2* dxy_tex = nullptr;    // VaFR: film offset per texel, in texel order
     int32_t* ord = nullptr;       // VaFR: texel index of each trace-order slot
     int32_t* blk_col = nullptr;   // VaFR: column of texel 256 b (per-texel kernels' block start)
-    int4* fxaa_tile = nullptr;    // VaFR: tiles of the LP anti-aliasing (first column, sector, sectors, 0)
+    int4* fxaa_tile = nullptr;    // VaFR: tiles of the LP anti-aliasing (first column, sector, sectors, narrow)
     int32_t n_fxaa_tiles = 0;
     float2* u_of_rho = nullptr;   // VaFR: (u_k, u_{k+1} - u_k) at rho_k = k h, k <= kURhoN
     double* lm_z = nullptr;       // LMFR: z_i per column
@@ -390,7 +390,9 @@ constexpr int kTexelBlock = 256;   // texels per workgroup of per-texel kernels
 // LP anti-aliasing over all texels of a VaFR layout, in tiles of kFxaaCols
 // columns by a sector of at most kFxaaRows rows of each.
 constexpr int kFxaaCols = 4, kFxaaRows = 64, kFxaaThreads = 256;
-int launch_fxaa(const LayoutDev& ld, int32_t n_cols, const float* in, float* out, hipStream_t stream);
+constexpr int64_t kFxaaDirect = 131072;   // layouts of fewer texels take the direct form (fxaa.hip)
+int launch_fxaa(const LayoutDev& ld, int32_t n_cols, int64_t n_texels, const float* in, float* out,
+                hipStream_t stream);
 
 // vafr_shade_lp_rep on a given workspace (validation included); the
 // allocation-free entry point passes its static scratch array.
