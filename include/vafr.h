@@ -96,7 +96,9 @@ int vafr_acuity_capped(const vafr_acuity* in, double cap_cpd, double* ecc_out, d
                        int32_t* n_out);
 
 /* Pinhole camera: eye position and an orthonormal basis; the film plane is
- * at unit distance along forward, film y points along -up. */
+ * at unit distance along forward, film y points along -up.  (A basis scaled as
+ * a whole gives the same hits; rays whose largest direction component leaves
+ * [2^-10, 2^20] are traced by a slower form of the box test.) */
 typedef struct {
     float eye[3], right[3], up[3], forward[3];
 } vafr_camera;
@@ -219,12 +221,13 @@ typedef struct {
 
 int vafr_scene_get_info(vafr_scene scene, vafr_scene_info* out);
 
-/* Host copies of the BVH for structural checks: nodes[16 * n_nodes] as
- * stored on the device (per node: origin x, y, z, scale z; 8-bit plane
+/* Host copies of the BVH for structural checks: nodes[16 * n_nodes] as the
+ * builder makes them (per node: origin x, y, z, scale z; 8-bit plane
  * codes of four child boxes, x-lo, x-hi, y-lo, y-hi, z-lo, z-hi, child c in
  * byte c, then scale x, scale y (FP32 powers of two); four child references,
- * INT32_MIN for an empty slot) and
- * tri_order[n_tris] (original id of each stored triangle).  Either may be
+ * INT32_MIN for an empty slot, whose codes are 0) and
+ * tri_order[n_tris] (original id of each stored triangle).  The device copy
+ * has another scaling and other codes in empty slots.  Either may be
  * NULL. */
 int vafr_scene_export(vafr_scene scene, float* nodes, int32_t* tri_order);
 

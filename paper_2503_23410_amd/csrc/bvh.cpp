@@ -245,7 +245,7 @@ struct Packer {
         float lo[4][3], hi[4][3];
         int32_t ref[4] = {kEmptyRef, kEmptyRef, kEmptyRef, kEmptyRef};
         for (int q = 0; q < 4; ++q) {
-            for (int a = 0; a < 3; ++a) {   // an empty slot: [+inf, +inf], skipped by its reference
+            for (int a = 0; a < 3; ++a) {   // an empty slot: [+inf, +inf], not quantised
                 lo[q][a] = INFINITY;
                 hi[q][a] = INFINITY;
             }
@@ -265,7 +265,7 @@ struct Packer {
             uint8_t ql[4], qh[4];
             biased[a] = quantise_axis(org[a], top, k, lo, hi, a, ql, qh);
             for (int q = 0; q < 4; ++q) {
-                // empty slots keep codes 0 / 0; the traversal skips them by reference
+                // empty slots keep codes 0 / 0 here (format_nodes turns them inside out)
                 code_lo[a] |= (uint32_t)(q < k ? ql[q] : 0) << (8 * q);
                 code_hi[a] |= (uint32_t)(q < k ? qh[q] : 0) << (8 * q);
             }

@@ -240,7 +240,8 @@ __device__ __forceinline__ float code(uint32_t w, int c) { return (float)((w >> 
 // eighth of the padding of every stored box while every |o| component is at
 // most TraceView::fma_origin_limit; results below 2^-126 lose at most 2^-49
 // in distance.  So it needs no exit scale either.  An empty slot's codes are
-// 255 / 0, a box turned inside out by more than those errors: never met.
+// 255 / 0, a box turned inside out by at least 2 pad per axis, sixteen times
+// those errors: never met (its reference is not looked at).
 // Callers check the origin limit and the direction's range per wave.
 // Against byte conversions, compares and selects on unscaled distances, this
 // form and the stack's and loop's bookkeeping below measured: one eye on the
@@ -250,8 +251,9 @@ __device__ __forceinline__ float code(uint32_t w, int c) { return (float)((w >> 
 //
 // General form (any finite origin and direction): each plane is decoded as
 // fmaf(q, s, g), which the builder checked lies outside the child's padded
-// box, and tested in the subtract-multiply form with unscaled distances;
-// empty slots are skipped by their reference.
+// box (up to the 2^-49 that an origin below 2^-26 loses in the device format,
+// a billionth of the padding), and tested in the subtract-multiply form with
+// unscaled distances; empty slots are skipped by their reference.
 //
 // kSeg: the ray is followed over [t_lo, tlim] only (distances as the form
 // scales them), and may have narrowed tlim beforehand also as an any-hit ray.

@@ -105,10 +105,17 @@ int layout_device(vafr_layout L, const LayoutDev** out);
 //   ref  = the four child references.
 // Every decoded plane, computed as fmaf(code, scale, origin), lies outside
 // the child's padded FP32 box (the builder checks each one).
-// On the device (after format_nodes) origins are stored times 2^-100 and
-// scales times 2^49, for the traversal's fast slab form.
-// ref >= 0: internal node index; ref == kEmptyRef: no child (skipped by its
-// reference); otherwise a leaf, ~ref = first << 3 | (count-1).
+// ref >= 0: internal node index; ref == kEmptyRef: no child; otherwise a leaf,
+// ~ref = first << 3 | (count-1).
+// This is the host's and vafr_scene_export's format.  The traversal reads
+// another one, which format_nodes makes of an uploaded copy and without which
+// it must not run: origins times 2^-100 and scales times 2^49, for the fast slab
+// form, and in empty slots codes 255 / 0 for the low / high planes (0 / 0 on the
+// host).  The fast form does not look at references: it rejects an empty slot
+// because its box is inside out, low planes 255 scale >= 2 pad beyond the high
+// ones on every axis (the node's box holds a padded child), while roundings
+// move each plane by at most pad / 8 for the origins that the form takes.  The
+// general form rejects it by its reference.
 struct alignas(16) BvhNode {
     float4 org;
     uint4 q0, q1;
