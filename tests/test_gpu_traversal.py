@@ -12,6 +12,8 @@ pytestmark = pytest.mark.gpu
 # 8 x 8 pixel tiles, two per 128-ray workgroup, chunks of 8 workgroups dealt
 # to 8 XCDs: fewer workgroups than XCDs, one chunk per XCD less one, exactly
 # one, one more, and several chunks with a ragged rest.
+# (Those are the workgroups of a batch; a per-view launch has one tile per
+# 64-ray workgroup and chunks of 16.  Batches: test_gpu_xcd.py.)
 @pytest.mark.parametrize("tiles", [1, 2, 13, 16, 17, 126, 128, 130, 254, 1000, 1023, 1024, 1040, 2047])
 def test_full_shade_traces_every_tile_once(O, tiles):
     import torch
