@@ -20,12 +20,13 @@
 // mostly ends after a step or two); what lies outside is read from the LP
 // buffer.  Straight from the LP buffer (one thread per texel, up to 24
 // dependent rounds of 16-byte gathers) the vector L1's return path was 70%
-// busy at three resident waves per SIMD: 48 us for the paper's layout on the
-// 4.52M terrain (nearly every texel an edge) and 29 us on the soup, now 35 and
-// 24 us; a buffer without edges takes 14 instead of 13 us.  What bounds it now
+// busy at three resident waves per SIMD.  The paper's layout (1.06M texels),
+// calls back to back, without -> with the window: 4.52M terrain (nearly every
+// texel an edge) 46 -> 31 us, 1.13M terrain 49 -> 32, 4,096-triangle soup 28 ->
+// 22, noise 63 -> 41, a buffer without edges 12.5 -> 12.2.  What bounds it now
 // is the search: a wave walks on until the last of its 64 searches has ended.
 // Windows of 2 to 16 columns on either side and 4 to 10 rows, and tiles of 8,
-// 12 or 16 columns, measured 34-44 us.
+// 12 or 16 columns, measured 34-44 us on the 4.52M terrain.
 //
 // A layout of fewer than kFxaaDirect texels does not fill the chip, and what
 // counts is how long one workgroup takes: it is faster without the window, one

@@ -14,17 +14,17 @@
 // of each pixel are then read from LDS.  In nearly every tile of a large
 // display the staged rows do not cross the seam: such tiles take sample_rows,
 // the others sample_vafr (178 VALU instructions per pixel), with the same
-// arithmetic.  A texel outside the
-// staged region (not expected, but the bound is computed in floating point)
-// is read from the LP buffer instead, so the result never depends on the
-// bound.  Tiles whose footprint exceeds the LDS budget -- those within a few
+// arithmetic.  A texel outside the staged region (not expected, but the bound
+// is computed in floating point) is read from the LP buffer instead, so the
+// result never depends on the bound.  Tiles whose footprint exceeds the LDS budget -- those within a few
 // degrees of the gaze point, where one display pixel maps to about one texel
 // or the tile surrounds the gaze -- read every texel from the LP buffer.
 //
-// Measured, one view, all tiles in the general sampler -> now: 7680x4320 141 /
-// 127 -> 111 / 97 us (centred / off-centre gaze), 3840x2160 45 / 41 -> 38 / 34
-// us, 1921x1083 20 -> 15 us; binocular pairs at 8K 192 -> 180 us (6.1 TB/s, at
-// the rate of a store-only probe); 16 mixed views (unpaired) 1.22 -> 0.84 ms.
+// What bounds it is the store rate: binocular pairs at 8K run at 6.8 - 6.9 TB/s,
+// where a fill reaches 6.86 on this card.  Measured, all tiles in the general
+// sampler -> now: one view 7680x4320 134 -> 88 us, 3840x2160 42 -> 33 us,
+// 1921x1083 20 -> 14 us; binocular pairs at 8K 174 -> 160 us; 16 mixed views
+// (unpaired) 1.21 -> 0.83 ms.
 //
 // A view may carry a second LP buffer and image with the same layout, gaze
 // and display (the other eye of a binocular frame): every pixel then reads
@@ -36,9 +36,9 @@
 // (which receive consecutive ids in turn) write neighbouring tiles of the
 // same tile row at the same time.  Giving each XCD a contiguous band of rows
 // instead keeps each XCD's LP reads in its own L2, but makes the stores --
-// 97% of the kernel's traffic -- slower: a store-only probe of this pattern
-// drops from 6.2 to 5.6 TB/s, and the kernel from 213 to 217 us per
-// binocular 8K frame.
+// 97% of the kernel's traffic -- slower: a store-only probe of 64 x 32 tiles
+// drops from 6.2 to 5.6 TB/s, and the kernel took 217 instead of 213 us per
+// binocular 8K frame when its tiles were of that size.
 #include "vafr_internal.h"
 
 namespace vafr {

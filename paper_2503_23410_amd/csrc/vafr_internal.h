@@ -259,7 +259,8 @@ constexpr int kTraceBlockDefault = 128;   // batches
 // keeps its slots until its last wave ends: one-wave workgroups measured 259 /
 // 235 / 251 us per eye on the 4.52M terrain against 267 / 242 / 252 of two
 // waves (256 rays: 273 / 244 / 259), 2560x1440 full resolution 435 against 450
-// us (472), LMFR(1.8) at 8K 1.21 against 1.25 ms (1.30).
+// us (472), LMFR(1.8) at 8K 1.21 against 1.25 ms (1.30).  (All before the rays
+// waited in LDS, see shade_lambert.)
 constexpr int kTraceBlockSingle = 64;
 // counters != nullptr selects the diagnostic work-counting pass.
 int launch_trace(const TraceView& v, hipStream_t stream, unsigned long long* counters = nullptr);
