@@ -971,14 +971,15 @@ __device__ __forceinline__ void trace_item(const TraceView& v, int64_t k, int* s
 
 // Register budget of the traversal kernels, in waves per SIMD (512 VGPRs per
 // lane over that many waves, in allocation steps of 8).  Kernels that trace
-// whole paths in one pass (per-view path mode, the reprojection's list)
-// keep five waves (at most 96 VGPRs): below that their extra state spills.
+// whole paths in one pass (per view and over the reprojection's list) keep
+// five waves (at most 96 VGPRs): below that their extra state spills.
 // The Lambert-only kernels, which keep the primary ray's direction and
 // output slot elsewhere while it is traced, and the phased path-mode
 // kernels, which hold no path state across a traversal, take the eight-wave
-// budget (64 VGPRs); at the 69 VGPRs the former take otherwise, a
-// 2560x1440 full-resolution view on the 1.13M terrain takes 0.50 ms instead
-// of 0.45 and LMFR(1.8) at 8K 1.36 ms instead of 1.25.
+// budget (64 VGPRs); at the 69 VGPRs the former take otherwise, an eye of
+// 1.06M rays on the 1.13M terrain takes 210 us instead of 198 and LMFR(1.8) at
+// 8K 1.08 ms instead of 1.01.  The Lambert-shaded list, which also holds the
+// rays shared by four lanes, needs 69.
 #define kTraceWaves(lambert) __attribute__((amdgpu_waves_per_eu((lambert) ? 8 : 5)))
 #define kListWaves(lambert) __attribute__((amdgpu_waves_per_eu((lambert) ? 6 : 5)))
 #define kBatchWaves(lambert, phased) __attribute__((amdgpu_waves_per_eu((phased) || (lambert) ? 8 : 5)))
