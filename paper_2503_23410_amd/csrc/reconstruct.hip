@@ -264,13 +264,19 @@ __device__ __forceinline__ void sample_vafr(const ReconView& v, const Stage& st,
 //    in FP64: ln q is log1p(q - 1) for q > 1/2, so it keeps its relative
 //    precision as r approaches R, and log(q) below (where q - 1 rounded to
 //    FP32 would lose the small q's digits).
+// kOne: one pixel at a time.  Its two logarithms are branches (3840x2160 in a
+// batch of one row per thread: both and a select 73 us, LMFR 51; branches 42
+// and 42); two pixels at a time overlap both logarithms of each better than
+// they branch (640x361, 8 rows: 13.7 us, branches 14.2).  The difference from 1
+// is formed by one FMA either way.
+template <bool kOne>
 __device__ __forceinline__ float lafr_u(const ReconView& v, float z, double r2) {
     if (z <= v.lf_zef) return powf(z * v.lf_fa1, v.lf_inv_fa);
-    // (branches, not both logarithms and a select: one row per thread in a
-    // batch, 3840x2160, LaFR 73 -> 42 us, LMFR 51 -> 42 us)
     const double q = r2 * v.lf_inv_r2;
     float lq;
-    if (q > 0.5) {
+    if (!kOne) {
+        lq = q > 0.5 ? log1pf((float)fma(r2, v.lf_inv_r2, -1.0)) : logf((float)q);
+    } else if (q > 0.5) {
         float qm = (float)fma(r2, v.lf_inv_r2, -1.0);
         __asm__ volatile("" : "+v"(qm));
         lq = log1pf(qm);
@@ -293,13 +299,14 @@ struct DenseTaps {
 
 // Pixel (x, y) of an LMFR / LaFR view: the offset from the gaze point is
 // formed in FP64 (the gaze is a continuous FP64 position), then rounded.
+template <bool kOne>
 __device__ __forceinline__ DenseTaps dense_taps(const ReconView& v, int x, int y) {
     const double dxd = (double)x + v.lm_cx, dyd = (double)y + v.lm_cy;
     const float dx = (float)dxd, dy = (float)dyd;
     const double r2 = dxd * dxd + dyd * dyd;
     const float r = fmaxf(__builtin_amdgcn_sqrtf((float)r2), 1.0f);
     const float z = __log2f(r) * v.inv_L;                     // Eq. (1); inv_L = ln 2 / L
-    float u = (v.lf_on ? lafr_u(v, z, r2)                                      // Eq. (15)
+    float u = (v.lf_on ? lafr_u<kOne>(v, z, r2)                                      // Eq. (15)
                        : v.alpha == 4.0f ? (z * z) * (z * z) : __powf(z, v.alpha)) * (float)v.n_cols;   // Eq. (14)
     u = fminf(fmaxf(u, 0.5f), (float)v.n_cols - 0.5f);
     const float a = u - 0.5f;
@@ -555,7 +562,7 @@ __device__ __forceinline__ void recon_tile(const ReconView& v, int id, Stage& st
             float4 c[kRows][4];
 #pragma unroll
             for (int q = 0; q < kRows; ++q) {
-                t[q] = dense_taps(v, x, y0 + ty + q);
+                t[q] = dense_taps<kRows == 1>(v, x, y0 + ty + q);
                 c[q][0] = ld4(lp, t[q].o00);
                 c[q][1] = ld4(lp, t[q].o01);
                 c[q][2] = ld4(lp, t[q].o10);
