@@ -677,7 +677,8 @@ extern "C" int vafr_batch_autotune(vafr_batch b, const vafr_view* views, int32_t
     }
     if (!rc) {
         // (4 rows stand for the same launch as 2 where every view is a pair)
-        const bool pairs = std::all_of(b->rv.begin(), b->rv.end(), [](const ReconView& r) { return r.lp2 != nullptr; });
+        const bool pairs = !b->rv.empty() && std::all_of(b->rv.begin(), b->rv.end(),
+                                                         [](const ReconView& r) { return r.lp2 != nullptr; });
         if (pairs && best.recon_rows == 4) best.recon_rows = 2;
         const vafr_batch_config base = best;
         for (int rows : {1, 2, 4, 8}) {
